@@ -324,7 +324,7 @@ extern "C" int sf_get_segment(sf_t sf, int64_t s, sf_segment_info *seg) {
   if (s < 0 || s >= (int64_t)sf->segments.size()) return SF_ERR_ARG;
   const Segment &S = sf->segments[(size_t)s];
   seg->rank = S.rank;
-  seg->nleaves = (int64_t)S.members.size();
+  seg->nleaves = S.n;
   seg->root = S.root;
   seg->leaf = S.leaf;
   return SF_OK;

@@ -101,7 +101,8 @@ struct DevWChunk {  // a level-0 chunk of a large root, as placed in a window
 // ------------------------------------------------------------- host plan
 struct Segment {
   int64_t rank;
-  std::vector<int64_t> members;  // leaf indices, ascending
+  int64_t n = 0;                 // leaves
+  std::vector<int64_t> members;  // leaf indices, ascending (during the analysis)
   sf_pattern root{}, leaf{};
 };
 
@@ -116,6 +117,7 @@ struct HostPlan {
   std::vector<DevTile> tiles;
   int32_t tile_leaves = kTileLeaves;  // leaves per tile of this SF
   bool all_contig = false;            // every segment contiguous on both sides (few segments)
+  bool rooted = false;                // Reduce walks the (single-leaf) roots in ascending order
   std::vector<int32_t> ridx;      // root index per processed leaf (generic root sides)
   std::vector<int32_t> ridx_hot;  // same, hot roots encoded as -(h+1)
   std::vector<int32_t> lidx;      // leaf slot per processed leaf (generic leaf sides)
