@@ -3,9 +3,12 @@
 // off-diagonal block B over the ghost vector lvec, and
 //   y = M x:    SFBcast(x -> lvec) overlapped with y = A x, then y += B lvec;
 //   y = M^T x:  y = A^T x, lvec = B^T x, then SFReduce SUM(lvec -> y).
-// The CSR products are plain HIP kernels: G lanes of a wavefront per row
-// (G a power of two near the mean row length), each lane striding over the
-// row's entries, the lanes' partial sums combined by shuffles.
+// The CSR products are plain HIP kernels: a wavefront per 64 short rows whose
+// entries it loads coalesced and sums out of the LDS (k_csr_rows, in column
+// panels when x does not fit an L2), or, for long or very uneven rows, G lanes
+// of a wavefront per row (G a power of two near the mean row length), each
+// lane striding over the row's entries, the lanes' partial sums combined by
+// shuffles (k_csr_spmv).
 #include <algorithm>
 #include <new>
 #include <vector>
@@ -22,7 +25,14 @@ struct sf_csr_s {
   double *values = nullptr;
   hipEvent_t ev = nullptr;  // the Bcast's completion, for the overlapped product
   int device = -1;
-  int group = 1;  // lanes per row
+  int group = 1;  // lanes per row of k_csr_spmv
+  // k_csr_rows: the entries by group of 64 rows, column panel, row
+  // (panels 0: k_csr_spmv).  With several panels colidx / values hold that
+  // order in place of the CSR order.
+  int panels = 0;
+  int64_t ngroups = 0;
+  uint32_t *gbase = nullptr;   // [ngroups * panels + 1] first entry of each group's panel
+  uint16_t *starts = nullptr;  // [ngroups * panels * 64] first entry of each row, relative to gbase
 };
 
 namespace sfi {
@@ -47,6 +57,133 @@ __global__ __launch_bounds__(kBlock) void k_csr_spmv(const int64_t *__restrict__
   if (ok && sub == 0) y[row] = accumulate ? y[row] + s : s;
 }
 
+// y = A x (or y += A x) over one column panel, a wavefront per group of 64
+// rows: it loads the group's column indices and values coalesced, U * 64 at a
+// time, gathers x for all of them, and leaves (value, x) in its own part of
+// the LDS; each lane then sums its row's products there with four running
+// fused sums, combined pairwise.  No load depends on a row's own offset, so a
+// wavefront has U gathers per lane in flight whatever its rows' lengths.
+//
+// Bound by the gathers: a request per entry, served from the L2 at 235 G/s
+// while x fits (190 beside the entry streams), at 115 G/s for an x of 8 MB and
+// 78 G/s for 16 MB (random columns).  So an x beyond an L2 is cut into panels,
+// one launch per panel (the launch boundary keeps every XCD on one panel),
+// each adding to y.  Measured on 1M rows x 15 random entries, the matrix read
+// from HBM (us): k_csr_spmv 158; here 160 with one panel, 124 with two, 114
+// with three, 124 with four.  2M rows (x of 16 MB): 411 with one panel, 254
+// with three, 248 with five.  250K rows x 16 entries: 51 -> 42; 1M rows x 4
+// entries over an x of 2 MB: 33.3 -> 30.3; 300K rows x 15 over 2.4 MB, the
+// matrix in the Infinity Cache: 30 -> 26.  Set aside: one launch whose
+// resident wavefronts sweep the panels together (no faster than 111 on warm
+// matrices against 92: they drift apart), panels bound to XCDs with partial
+// results (103 + 9 for their sum), the next group's loads issued ahead (108
+// against 108 on a matrix from HBM; fewer, longer wavefronts 120).  Sums of
+// fused products are closer to the exact ones than the lane tree of k_csr_spmv
+// (15 entries: 1.02e-16 against 1.10e-16; three panels 1.09e-16).
+constexpr int kCsrAcc = 4;
+template <int U>
+__global__ __launch_bounds__(kBlock) void k_csr_rows(const uint32_t *__restrict__ gbase,
+                                                     const uint16_t *__restrict__ starts,
+                                                     const int32_t *__restrict__ colidx,
+                                                     const double *__restrict__ values, int64_t nrows, int64_t ngroups,
+                                                     int panels, int panel, const double *__restrict__ x,
+                                                     double *__restrict__ y, int accumulate) {
+  constexpr int kCap = U * 64;
+  __shared__ double2 stage[kBlock / 64][kCap];
+  const int lane = threadIdx.x & 63;
+  double2 *lds = stage[threadIdx.x >> 6];
+  const int64_t g = (int64_t)blockIdx.x * (kBlock / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (g >= ngroups) return;
+  const int64_t gp = g * panels + panel;
+  const uint32_t b = gbase[gp];
+  const int n = (int)(gbase[gp + 1] - b);
+  const int s0 = starts[gp * 64 + lane];
+  const int64_t row = g * 64 + lane;
+  const double y0 = accumulate && row < nrows ? y[row] : 0.0;
+  const int32_t *cb = colidx + b;
+  const double *vb = values + b;
+  int s1 = 0;
+  double acc[kCsrAcc] = {};
+  for (int c0 = 0; c0 < n; c0 += kCap) {
+    // positions past n repeat the last entry; no row reads them
+    int32_t col[U];
+    double v[U], xv[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) col[u] = cb[min(c0 + u * 64 + lane, n - 1)];
+#pragma unroll
+    for (int u = 0; u < U; u++) v[u] = vb[min(c0 + u * 64 + lane, n - 1)];
+    if (c0 == 0) {
+      const int next = __shfl_down(s0, 1);
+      s1 = lane == 63 ? n : next;
+    }
+#pragma unroll
+    for (int u = 0; u < U; u++) xv[u] = x[col[u]];
+#pragma unroll
+    for (int u = 0; u < U; u++) lds[u * 64 + lane] = make_double2(v[u], xv[u]);
+    // the stage is the wavefront's own and its LDS accesses complete in order:
+    // only the compiler has to keep them so
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const int z = min(s1 - c0, kCap);
+    for (int j = max(s0 - c0, 0); j < z; j += kCsrAcc) {
+      double2 t[kCsrAcc];
+#pragma unroll
+      for (int k = 0; k < kCsrAcc; k++) t[k] = lds[min(j + k, kCap - 1)];
+#pragma unroll
+      for (int k = 0; k < kCsrAcc; k++) acc[k] = j + k < z ? fma(t[k].x, t[k].y, acc[k]) : acc[k];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  }
+  if (row < nrows) y[row] = y0 + ((acc[0] + acc[1]) + (acc[2] + acc[3]));
+}
+
+// The tables of k_csr_rows from the CSR arrays and, for several panels of pw
+// columns, the entries in (group, panel, row) order, a row's entries of a
+// panel in their stored order (pcol, pval).  A wavefront per group, a lane per
+// row; a group's entries stay in its range of the CSR arrays, so no scan over
+// the groups is needed.  Runs once per matrix.
+__global__ __launch_bounds__(kBlock) void k_csr_panelize(const int64_t *__restrict__ rowptr,
+                                                         const int32_t *__restrict__ colidx,
+                                                         const double *__restrict__ values, int64_t nrows,
+                                                         int64_t ngroups, int panels, int pw,
+                                                         uint32_t *__restrict__ gbase, uint16_t *__restrict__ starts,
+                                                         int32_t *__restrict__ pcol, double *__restrict__ pval) {
+  const int lane = threadIdx.x & 63;
+  const int64_t g = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+  if (g >= ngroups) return;
+  const int64_t row = g * 64 + lane;
+  const int64_t k0 = rowptr[min(row, nrows)], k1 = rowptr[min(row + 1, nrows)];
+  int64_t base = rowptr[g * 64];
+  for (int p = 0; p < panels; p++) {
+    const int32_t c0 = p * pw, c1 = p + 1 < panels ? c0 + pw : INT32_MAX;
+    int cnt = 0;
+    if (panels == 1)
+      cnt = (int)(k1 - k0);
+    else
+      for (int64_t k = k0; k < k1; k++) cnt += colidx[k] >= c0 && colidx[k] < c1;
+    int inc = cnt;
+#pragma unroll
+    for (int d = 1; d < 64; d *= 2) {
+      const int o = __shfl_up(inc, d);
+      if (lane >= d) inc += o;
+    }
+    if (lane == 0) gbase[g * panels + p] = (uint32_t)base;
+    starts[(g * panels + p) * 64 + lane] = (uint16_t)(inc - cnt);
+    if (panels > 1) {
+      int64_t at = base + inc - cnt;
+      for (int64_t k = k0; k < k1; k++) {
+        const int32_t c = colidx[k];
+        if (c >= c0 && c < c1) {
+          pcol[at] = c;
+          pval[at] = values[k];
+          at++;
+        }
+      }
+    }
+    base += __shfl(inc, 63);
+  }
+  if (g == ngroups - 1 && lane == 0) gbase[ngroups * panels] = (uint32_t)base;
+}
+
 static int pick_group(int64_t nrows, int64_t nnz) {
   const double mean = nrows > 0 ? (double)nnz / (double)nrows : 1.0;
   int g = 1;
@@ -54,8 +191,20 @@ static int pick_group(int64_t nrows, int64_t nnz) {
   return g;
 }
 
+static unsigned group_blocks(int64_t ngroups) { return (unsigned)((ngroups + kBlock / 64 - 1) / (kBlock / 64)); }
+
 static int csr_launch(const sf_csr_s *a, const double *x, double *y, int accumulate, hipStream_t st) {
   if (a->nrows == 0) return SF_OK;
+  if (a->panels > 0) {
+    // entries in flight: a whole group's panel where that is at most 384
+    const bool four = a->nnz <= 256 * a->ngroups * a->panels;
+    for (int p = 0; p < a->panels; p++)
+      hipLaunchKernelGGL(four ? k_csr_rows<4> : k_csr_rows<6>, dim3(group_blocks(a->ngroups)), dim3(kBlock), 0, st,
+                         a->gbase, a->starts, a->colidx, a->values, a->nrows, a->ngroups, a->panels, p, x, y,
+                         accumulate || p > 0 ? 1 : 0);
+    hipError_t e = hipGetLastError();
+    return e == hipSuccess ? SF_OK : set_hip_error(e);
+  }
   const int64_t threads = a->nrows * a->group;
   const unsigned g = (unsigned)((threads + kBlock - 1) / kBlock);
 #define SF_CSR(G)                                                                                                 \
@@ -81,8 +230,93 @@ static void csr_free(sf_csr_s *a) {
   if (a->rowptr) (void)hipFree(a->rowptr);
   if (a->colidx) (void)hipFree(a->colidx);
   if (a->values) (void)hipFree(a->values);
+  if (a->gbase) (void)hipFree(a->gbase);
+  if (a->starts) (void)hipFree(a->starts);
   if (a->ev) (void)hipEventDestroy(a->ev);
   delete a;
+}
+
+// Whether k_csr_rows takes the matrix, and with how many panels.
+//  * Rows of at most kCsrRowMean entries a panel on average, none far above
+//    that: a lane sums its row alone, so one long row would hold up its
+//    wavefront, and four running sums stay as exact as the lane tree only up
+//    to about that length.
+//  * One panel while x is at most kCsrOnePanel bytes (500K rows x 15 entries
+//    over 4 MB: 46.9 us with one panel or two) or a group's columns lie within
+//    a panel's width (a band); else panels of about kCsrPanelBytes that leave
+//    a row kCsrPanelMin entries in each (every further panel reads and writes
+//    y once more).
+constexpr double kCsrRowMean = 24.0;
+constexpr int64_t kCsrOnePanel = 9 << 19;     // 4.5 MiB; an XCD's L2 is 4 MiB
+constexpr int64_t kCsrPanelBytes = 11 << 18;  // 2.75 MiB
+constexpr double kCsrPanelMin = 4.0;
+constexpr int kCsrPanelMax = 8;
+
+static int csr_panels(const sf_csr_s *a) {
+  if (a->nnz == 0 || a->nnz >= INT32_MAX) return 0;
+  const double mean = (double)a->nnz / (double)a->nrows;
+  int64_t longest = 0;
+  for (int64_t i = 0; i < a->nrows; i++) longest = std::max(longest, a->h_rowptr[i + 1] - a->h_rowptr[i]);
+  int panels = 1;
+  const int64_t xb = a->ncols * 8;
+  if (xb > kCsrOnePanel) {
+    const int64_t want = std::min<int64_t>((xb + kCsrPanelBytes - 1) / kCsrPanelBytes, kCsrPanelMax);
+    panels = (int)std::max<int64_t>(1, std::min<int64_t>(want, (int64_t)(mean / kCsrPanelMin)));
+    // mean column span of a sample of the groups
+    const int64_t groups = (a->nrows + 63) / 64, step = std::max<int64_t>(1, groups / 256);
+    double span = 0.0;
+    int64_t sampled = 0;
+    for (int64_t g = 0; g < groups; g += step) {
+      const int64_t k0 = a->h_rowptr[g * 64], k1 = a->h_rowptr[std::min(a->nrows, g * 64 + 64)];
+      if (k0 == k1) continue;
+      const auto mm = std::minmax_element(a->h_colidx.begin() + k0, a->h_colidx.begin() + k1);
+      span += (double)(*mm.second - *mm.first);
+      sampled++;
+    }
+    if (span * panels <= (double)a->ncols * (double)sampled) panels = 1;
+  }
+  if (mean > kCsrRowMean * panels || (double)longest > 4.0 * mean + 32.0 || longest > 1000) return 0;
+  return panels;
+}
+
+static int csr_rows_plan(sf_csr_s *a) {
+  const int panels = csr_panels(a);
+  if (panels == 0) return SF_OK;
+  const int64_t ngroups = (a->nrows + 63) / 64;
+  const size_t gp = (size_t)ngroups * panels;
+  uint32_t *gbase = nullptr;
+  uint16_t *starts = nullptr;
+  int32_t *pcol = nullptr;
+  double *pval = nullptr;
+  hipError_t e = hipMalloc(&gbase, (gp + 1) * sizeof(uint32_t));
+  if (e == hipSuccess) e = hipMalloc(&starts, gp * 64 * sizeof(uint16_t));
+  if (e == hipSuccess && panels > 1) e = hipMalloc(&pcol, (size_t)a->nnz * 4);
+  if (e == hipSuccess && panels > 1) e = hipMalloc(&pval, (size_t)a->nnz * 8);
+  if (e == hipSuccess) {
+    const int pw = (int)((a->ncols + panels - 1) / panels);
+    hipLaunchKernelGGL(k_csr_panelize, dim3(group_blocks(ngroups)), dim3(kBlock), 0, nullptr, a->rowptr, a->colidx,
+                       a->values, a->nrows, ngroups, panels, pw, gbase, starts, pcol, pval);
+    e = hipGetLastError();
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+    if (e == hipSuccess && panels > 1) {
+      std::swap(a->colidx, pcol);
+      std::swap(a->values, pval);
+    }
+  }
+  if (pcol) (void)hipFree(pcol);
+  if (pval) (void)hipFree(pval);
+  if (e != hipSuccess) {
+    if (gbase) (void)hipFree(gbase);
+    if (starts) (void)hipFree(starts);
+    if (e != hipErrorOutOfMemory) return set_hip_error(e);
+    (void)hipGetLastError();  // no room for the tables: k_csr_spmv serves the matrix
+    return SF_OK;
+  }
+  a->gbase = gbase;
+  a->starts = starts;
+  a->ngroups = ngroups;
+  a->panels = panels;
+  return SF_OK;
 }
 
 static int csr_upload(sf_csr_s *a) {
@@ -98,7 +332,7 @@ static int csr_upload(sf_csr_s *a) {
   if (e == hipSuccess) e = hipEventCreateWithFlags(&a->ev, hipEventDisableTiming);
   if (e != hipSuccess) return e == hipErrorOutOfMemory ? SF_ERR_OOM : set_hip_error(e);
   a->group = pick_group(a->nrows, a->nnz);
-  return SF_OK;
+  return csr_rows_plan(a);
 }
 
 }  // namespace sfi

@@ -93,3 +93,50 @@ def test_csr_spmv_rows_of_every_length():
         torch.cuda.synchronize()
         want = oracle.csr_spmv(rowptr, colidx, vals, x, y0 if acc else None)
         assert np.all(np.abs(ty.cpu().numpy() - want) <= 1e-12 * scale)
+
+
+# rows of a wavefront's group and past it, entries around one stage (256 / 384),
+# x within one panel and cut into two, three and eight, a band, and rows too
+# uneven for the grouped kernel
+@pytest.mark.parametrize("nrows,ncols,low,high,kind", [
+    (1, 50, 3, 3, "random"), (63, 900, 0, 9, "random"), (64, 900, 4, 4, "random"), (65, 900, 4, 5, "random"),
+    (4097, 5000, 6, 6, "random"), (4100, 5000, 0, 40, "random"), (300, 700_000, 8, 8, "random"),
+    (1000, 1_000_001, 0, 30, "random"), (777, 3_000_000, 20, 60, "random"), (70_000, 700_000, 9, 15, "band"),
+    (500, 1_000_001, 2, 9, "first"), (500, 4000, 0, 400, "uneven")])
+def test_grouped_rows(nrows, ncols, low, high, kind):
+    rng = np.random.default_rng(nrows + ncols)
+    lens = rng.integers(low, high + 1, nrows)
+    if kind == "uneven":
+        lens[:] = 2
+        lens[nrows // 2] = 900
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    nnz = int(rowptr[-1])
+    if kind == "band":
+        rows = np.repeat(np.arange(nrows), lens)
+        colidx = np.clip(rows * (ncols // nrows) + rng.integers(-50, 50, nnz), 0, ncols - 1)
+    elif kind == "first":  # every column in the first panel but one in the last
+        colidx = rng.integers(0, 100, nnz)
+        colidx[-1] = ncols - 1
+    else:
+        colidx = rng.integers(0, ncols, nnz)
+    colidx = colidx.astype(np.int32)
+    vals, x, y0 = rng.standard_normal(nnz), rng.standard_normal(ncols), rng.standard_normal(nrows)
+    A = S.Csr(nrows, ncols, rowptr, colidx, vals)
+    scale = oracle.csr_spmv(rowptr, colidx, np.abs(vals), np.abs(x)) + np.abs(y0)
+    tx = torch.from_numpy(x).cuda()
+    for acc in (False, True):
+        got = []
+        for _ in range(2):  # bit-identical from run to run
+            ty = torch.from_numpy(y0).cuda()
+            A.spmv(tx, ty, accumulate=acc)
+            torch.cuda.synchronize()
+            got.append(ty.cpu().numpy())
+        want = oracle.csr_spmv(rowptr, colidx, vals, x, y0 if acc else None)
+        assert np.all(np.abs(got[0] - want) <= 1e-12 * scale)
+        assert got[0].tobytes() == got[1].tobytes()
+    At = A.transpose()
+    xt, tz = rng.standard_normal(nrows), torch.full((ncols,), np.nan, dtype=torch.float64, device="cuda")
+    At.spmv(torch.from_numpy(xt).cuda(), tz)
+    want = oracle.csr_spmv(rowptr, colidx, vals, xt, transpose=True, ncols=ncols)
+    scale = oracle.csr_spmv(rowptr, colidx, np.abs(vals), np.abs(xt), transpose=True, ncols=ncols)
+    assert np.all(np.abs(tz.cpu().numpy() - want) <= 1e-12 * scale)
