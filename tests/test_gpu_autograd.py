@@ -107,3 +107,30 @@ def test_checkpointed_equals_plain(knn):
         A.chain_loss(dsf, h, a, G, checkpoint=ck).backward()
         grads.append(h.grad.cpu().numpy())
     assert grads[0].tobytes() == grads[1].tobytes()     # deterministic path: identical bits
+
+
+@pytest.mark.parametrize("holes,extra", [(False, 0), (True, 0), (False, 5), (True, 5)])
+def test_unwritten_leaves_are_zero(knn, holes, extra):
+    """Slots that no leaf writes -- holes, and a buffer beyond the leaf space
+    -- are zero in the Bcast and in the gradient of the Reduce, also in memory
+    that held other values."""
+    rng = np.random.default_rng(6)
+    n, space = 300, 400 if holes else 300
+    iroot, il = rng.integers(0, 50, n), rng.permutation(space)[:n] if holes else rng.permutation(n)
+    if holes:
+        il[0] = space - 1 if space - 1 not in il else il[0]
+    sf = S.StarForest(50, iroot, il).setup()
+    dsf = A.DiffSF(sf, sf.leafspace + extra)
+    full = (dsf.leafspace, 4)
+    junk = torch.full(full, float("nan"), device="cuda")
+    del junk  # the next buffer of this size takes its memory
+    h = torch.from_numpy(rng.standard_normal((50, 4)).astype(np.float32)).cuda()
+    leaf = A.sf_bcast(dsf, h)
+    want = np.zeros(full, np.float32)
+    want[il] = h.cpu().numpy()[iroot]
+    assert leaf.cpu().numpy().tobytes() == want.tobytes()
+    m = torch.zeros(full, device="cuda", requires_grad=True)
+    junk = torch.full(full, float("nan"), device="cuda")
+    del junk
+    A.sf_reduce_sum(dsf, m, torch.zeros_like(h)).backward(h)
+    assert m.grad.cpu().numpy().tobytes() == want.tobytes()
