@@ -65,25 +65,23 @@ __device__ __forceinline__ void bw_move(const BatchItemDev &it, const BatchTile 
   const Word *root = (const Word *)it.root;
   Word *leaf = (Word *)it.leaf;
   for (int q0 = threadIdx.x; q0 < items; q0 += kBlock * LPT) {
-    Word v[LPT];
-    int64_t dst[LPT];
+    int t[LPT], c[LPT];
 #pragma unroll
     for (int u = 0; u < LPT; u++) {
-      const int q = q0 + u * kBlock;
-      dst[u] = -1;
-      if (q < items) {
-        const int lt = fdiv(q, it.magic_words);
-        const int c = q - lt * w;
-        const int t = bt.t0 + lt;
-        const int32_t r = seg_root_s(sg, it.ridx, t);  // indices and leaf writes stream
-        const int32_t l = seg_leaf_s(sg, it.lidx, t);
-        v[u] = root[(int64_t)r * w + c];
-        dst[u] = (int64_t)l * w + c;
-      }
+      const int q = min(q0 + u * kBlock, items - 1);
+      const int lt = fdiv(q, it.magic_words);
+      c[u] = q - lt * w;
+      t[u] = bt.t0 + lt;
     }
+    int32_t r[LPT], l[LPT];  // indices and leaf writes stream
+    seg_roots<LPT>(sg, it.ridx, t, r);
+    seg_leaves<LPT>(sg, it.lidx, t, l);
+    Word v[LPT];
+#pragma unroll
+    for (int u = 0; u < LPT; u++) v[u] = root[(int64_t)r[u] * w + c[u]];
 #pragma unroll
     for (int u = 0; u < LPT; u++)
-      if (dst[u] >= 0) st_stream(leaf + dst[u], v[u]);
+      if (q0 + u * kBlock < items) st_stream(leaf + (int64_t)l[u] * w + c[u], v[u]);
   }
 }
 
@@ -95,29 +93,28 @@ __device__ __forceinline__ void bw_red_atomic(const BatchItemDev &it, const Batc
   const T *leaf = (const T *)it.leaf;
   T *root = (T *)it.root;
   for (int q0 = threadIdx.x; q0 < items; q0 += kBlock * LPT) {
-    T v[LPT];
-    int64_t dst[LPT];
+    int t[LPT], c[LPT];
 #pragma unroll
     for (int u = 0; u < LPT; u++) {
-      const int q = q0 + u * kBlock;
-      dst[u] = -1;
-      if (q < items) {
-        const int lt = fdiv(q, it.magic_bs);
-        const int c = q - lt * bs;
-        const int t = bt.t0 + lt;
-        const int32_t r = seg_root_s(sg, it.ridx, t);  // indices and leaf reads stream
-        const int32_t l = seg_leaf_s(sg, it.lidx, t);
-        v[u] = ld_stream(leaf + (int64_t)l * bs + c);
-        dst[u] = (int64_t)r * bs + c;
-      }
+      const int q = min(q0 + u * kBlock, items - 1);
+      const int lt = fdiv(q, it.magic_bs);
+      c[u] = q - lt * bs;
+      t[u] = bt.t0 + lt;
     }
+    int32_t r[LPT], l[LPT];  // indices and leaf reads stream
+    seg_roots<LPT>(sg, it.ridx, t, r);
+    seg_leaves<LPT>(sg, it.lidx, t, l);
+    T v[LPT];
+#pragma unroll
+    for (int u = 0; u < LPT; u++) v[u] = ld_stream(leaf + (int64_t)l[u] * bs + c[u]);
 #pragma unroll
     for (int u = 0; u < LPT; u++) {
-      if (dst[u] < 0) continue;
+      if (q0 + u * kBlock >= items) continue;
+      T *rp = root + (int64_t)r[u] * bs + c[u];
       if (it.plain)
-        root[dst[u]] = Op<OP_SUM, T>::apply(root[dst[u]], v[u]);
+        *rp = Op<OP_SUM, T>::apply(*rp, v[u]);
       else
-        AtomicG<OP_SUM, T>::run(root + dst[u], v[u]);
+        AtomicG<OP_SUM, T>::run(rp, v[u]);
     }
   }
 }
@@ -175,10 +172,13 @@ __device__ __forceinline__ void bw_det_wave(const BatchItemDev &it, const BatchT
     const int n = it.toff[t + 1] - g0;
     const int m = n - lane * LPT;
     for (int c = 0; c < bs; c++) {
+      // (positions past the root's end repeat its last leaf; none is combined)
+      int32_t l[LPT];
+#pragma unroll
+      for (int s = 0; s < LPT; s++) l[s] = ld_stream(it.sl + g0 + min(lane * LPT + s, n - 1));
       T x[LPT];
 #pragma unroll
-      for (int s = 0; s < LPT; s++)
-        if (s < m) x[s] = ld_stream(leaf + (int64_t)ld_stream(it.sl + g0 + lane * LPT + s) * bs + c);
+      for (int s = 0; s < LPT; s++) x[s] = ld_stream(leaf + (int64_t)l[s] * bs + c);
 #pragma unroll
       for (int d = 1; d < LPT; d *= 2)
 #pragma unroll
@@ -209,34 +209,32 @@ __device__ __forceinline__ void bw_fop_atomic(const BatchItemDev &it, const Batc
   T *root = (T *)it.root;
   T *upd = (T *)it.upd;
   for (int q0 = threadIdx.x; q0 < items; q0 += kBlock * LPT) {
-    T v[LPT];
-    int64_t rp[LPT], lp[LPT];
+    int t[LPT], c[LPT];
 #pragma unroll
     for (int u = 0; u < LPT; u++) {
-      const int q = q0 + u * kBlock;
-      rp[u] = -1;
-      if (q < items) {
-        const int lt = fdiv(q, it.magic_bs);
-        const int c = q - lt * bs;
-        const int t = bt.t0 + lt;
-        const int32_t r = seg_root_s(sg, it.ridx, t);
-        const int32_t l = seg_leaf_s(sg, it.lidx, t);
-        lp[u] = (int64_t)l * bs + c;
-        v[u] = ld_stream(leaf + lp[u]);
-        rp[u] = (int64_t)r * bs + c;
-      }
+      const int q = min(q0 + u * kBlock, items - 1);
+      const int lt = fdiv(q, it.magic_bs);
+      c[u] = q - lt * bs;
+      t[u] = bt.t0 + lt;
     }
+    int32_t r[LPT], l[LPT];
+    seg_roots<LPT>(sg, it.ridx, t, r);
+    seg_leaves<LPT>(sg, it.lidx, t, l);
+    T v[LPT];
+#pragma unroll
+    for (int u = 0; u < LPT; u++) v[u] = ld_stream(leaf + (int64_t)l[u] * bs + c[u]);
 #pragma unroll
     for (int u = 0; u < LPT; u++) {
-      if (rp[u] < 0) continue;
+      if (q0 + u * kBlock >= items) continue;
+      T *rp = root + (int64_t)r[u] * bs + c[u];
       T old;
       if (it.plain) {
-        old = root[rp[u]];
-        root[rp[u]] = Op<OP_SUM, T>::apply(old, v[u]);
+        old = *rp;
+        *rp = Op<OP_SUM, T>::apply(old, v[u]);
       } else {
-        old = fetch_add_g(root + rp[u], v[u]);
+        old = fetch_add_g(rp, v[u]);
       }
-      st_stream(upd + lp[u], old);
+      st_stream(upd + (int64_t)l[u] * bs + c[u], old);
     }
   }
 }

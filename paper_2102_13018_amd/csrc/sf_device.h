@@ -272,12 +272,52 @@ __device__ __forceinline__ int32_t seg_root(const DevSegment &s, const int32_t *
 __device__ __forceinline__ int32_t seg_leaf(const DevSegment &s, const int32_t *__restrict__ lidx, int32_t t) {
   return s.leaf.kind == SF_PATTERN_GENERIC ? lidx[s.loff + t] : pat_index(s.leaf, t);
 }
-// The same, for index arrays read once per operation (streaming loads).
-__device__ __forceinline__ int32_t seg_root_s(const DevSegment &s, const int32_t *__restrict__ ridx, int32_t t) {
-  return s.root.kind == SF_PATTERN_GENERIC ? ld_stream(ridx + s.roff + t) : pat_index(s.root, t);
+// The indices of U leaves of a segment side at once.  The side's kind is
+// looked at once and no load is conditional (callers clamp t into the tile),
+// so all U loads are in flight together: an index load inside a bounds check
+// is waited for before the next one is issued, and its wait drains the gather
+// issued before it.
+template <int U>
+__device__ __forceinline__ void seg_roots(const DevSegment &s, const int32_t *__restrict__ ridx, const int (&t)[U],
+                                          int32_t (&r)[U]) {
+  if (s.root.kind == SF_PATTERN_GENERIC) {
+    const int32_t *p = ridx + s.roff;
+#pragma unroll
+    for (int u = 0; u < U; u++) r[u] = ld_stream(p + t[u]);
+  } else {
+#pragma unroll
+    for (int u = 0; u < U; u++) r[u] = pat_index(s.root, t[u]);
+  }
 }
-__device__ __forceinline__ int32_t seg_leaf_s(const DevSegment &s, const int32_t *__restrict__ lidx, int32_t t) {
-  return s.leaf.kind == SF_PATTERN_GENERIC ? ld_stream(lidx + s.loff + t) : pat_index(s.leaf, t);
+template <int U>
+__device__ __forceinline__ void seg_leaves(const DevSegment &s, const int32_t *__restrict__ lidx, const int (&t)[U],
+                                           int32_t (&l)[U]) {
+  if (s.leaf.kind == SF_PATTERN_GENERIC) {
+    const int32_t *p = lidx + s.loff;
+#pragma unroll
+    for (int u = 0; u < U; u++) l[u] = ld_stream(p + t[u]);
+  } else {
+#pragma unroll
+    for (int u = 0; u < U; u++) l[u] = pat_index(s.leaf, t[u]);
+  }
+}
+
+// f(U) with as many items per thread and round as the block's items fill (1,
+// 2 or 4): a round's loads are unconditional, so items past the end would
+// cost loads of their own (256^3 halo, one leaf per thread: the exchange took
+// 16.2 us with four, 15.2 with one).
+template <int U>
+struct Count {
+  static constexpr int value = U;
+};
+template <typename F>
+__device__ __forceinline__ void by_round(int items, F f) {
+  if (items <= kBlock)
+    f(Count<1>{});
+  else if (items <= 2 * kBlock)
+    f(Count<2>{});
+  else
+    f(Count<4>{});
 }
 
 // ------------------------------------------------------------- atomics
@@ -530,7 +570,10 @@ __device__ __forceinline__ Vec<T, NV> vop(const Vec<T, NV> &a, const Vec<T, NV> 
 // 2 and 4 (whose pairs never leave the block), and the block results are
 // combined at distances 8, 16, ... -- the same operands in the same order as
 // the tree over all D positions, with a fraction of its registers (which
-// keeps kernels with a 32-leaf class at a useful occupancy).
+// keeps kernels with a 32-leaf class at a useful occupancy).  Positions past
+// the end load the last value again and are not combined: a conditional load
+// waits for the one before it, so a root of 5 to 8 leaves took up to four
+// round trips (64 items in one launch: 267 -> 250 us).
 template <int D, typename V, typename Load, typename Comb>
 __device__ __forceinline__ V pw_tree(int n, Load load, Comb comb) {
   constexpr int BMAX = sizeof(V) >= 16 ? 4 : 8;
@@ -544,7 +587,7 @@ __device__ __forceinline__ V pw_tree(int n, Load load, Comb comb) {
       V x[B];
 #pragma unroll
       for (int p = 0; p < B; p++)
-        if (p < m) x[p] = load(k * B + p);
+        x[p] = load(min(k * B + p, n - 1));
 #pragma unroll
       for (int d = 1; d < B; d *= 2)
 #pragma unroll

@@ -23,11 +23,14 @@
 namespace sfi {
 
 // ===================================================================== Bcast
-// leaf[l] = root[r] as W words of type Word per unit.  2^sh blocks per
-// tile, each taking its share of the tile's leaves: on SFs with full-size
-// tiles the random root gathers want more, smaller blocks than the plan's
-// tiles (measured on the 16M-leaf Zipf SF: 106 us with a block per 1024-leaf
-// tile, 102 with a block per half; the halo's small tiles stay whole).
+// leaf[l] = root[r] as W words of type Word per unit.  2^sh blocks per tile,
+// each taking its share of the tile's leaves, so that a block's threads have
+// about four words each and gather them all at once.  Bound by the lines that
+// the random root reads fetch into the L2s (128 bytes for an 8-byte root).
+// Measured with 1 / 2 / 4 blocks per 1024-leaf tile (us): 16M leaves of 8
+// bytes on Zipf roots 95.8 / 99.7 / 106.6; two Bcasts of 2M leaves of 64 bytes
+// in the k-NN layer 227.5 / 224.1 / 222.6 of the whole pass, 1.2M leaves of 64
+// bytes with their Reduce 66.2 / 64.7 / 63.6.
 template <typename Word, int W>
 __global__ __launch_bounds__(kBlock) void k_bcast_move(const DevSegment *__restrict__ segs,
                                                        const DevTile *__restrict__ tiles,
@@ -44,28 +47,28 @@ __global__ __launch_bounds__(kBlock) void k_bcast_move(const DevSegment *__restr
   const DevSegment sg = segs[tl.seg];
   const int w = W > 0 ? W : wrt;
   const int items = (tl.t1 - tl.t0) * w;
-  constexpr int U = 4;  // loads in flight per thread (more, smaller blocks measured faster)
-  for (int q0 = threadIdx.x; q0 < items; q0 += kBlock * U) {
-    Word v[U];
-    int64_t dst[U];
+  by_round(items, [&](auto count) {
+    constexpr int U = decltype(count)::value;  // items per thread with all their loads in flight
+    for (int q0 = threadIdx.x; q0 < items; q0 += kBlock * U) {
+      int t[U], c[U];
 #pragma unroll
-    for (int u = 0; u < U; u++) {
-      const int q = q0 + u * kBlock;
-      dst[u] = -1;
-      if (q < items) {
-        const int t = tl.t0 + q / w;
-        const int c = q % w;
-        // indices and leaf writes stream (used once); root reads stay cached
-        const int32_t r = seg_root_s(sg, ridx, t);
-        const int32_t l = seg_leaf_s(sg, lidx, t);
-        v[u] = root[(int64_t)r * w + c];
-        dst[u] = (int64_t)l * w + c;
+      for (int u = 0; u < U; u++) {
+        const int q = min(q0 + u * kBlock, items - 1);
+        t[u] = tl.t0 + q / w;
+        c[u] = q % w;
       }
-    }
+      // indices and leaf writes stream (used once); root reads stay cached
+      int32_t r[U], l[U];
+      seg_roots<U>(sg, ridx, t, r);
+      seg_leaves<U>(sg, lidx, t, l);
+      Word v[U];
 #pragma unroll
-    for (int u = 0; u < U; u++)
-      if (dst[u] >= 0) st_stream(leaf + dst[u], v[u]);
-  }
+      for (int u = 0; u < U; u++) v[u] = root[(int64_t)r[u] * w + c[u]];
+#pragma unroll
+      for (int u = 0; u < U; u++)
+        if (q0 + u * kBlock < items) st_stream(leaf + (int64_t)l[u] * w + c[u], v[u]);
+    }
+  });
 }
 
 // leaf[l][c] = op(leaf[l][c], root[r][c]) element-wise.
@@ -78,14 +81,31 @@ __global__ __launch_bounds__(kBlock) void k_bcast_op(const DevSegment *__restric
   const DevTile tl = tiles[blockIdx.x];
   const DevSegment sg = segs[tl.seg];
   const int items = (tl.t1 - tl.t0) * bs;
-  for (int q = threadIdx.x; q < items; q += kBlock) {
-    const int t = tl.t0 + q / bs;
-    const int c = q % bs;
-    const int32_t r = seg_root(sg, ridx, t);
-    const int32_t l = seg_leaf(sg, lidx, t);
-    T *p = leaf + (int64_t)l * bs + c;
-    st(p, Op<OP, T>::apply(ld(p), ld(root + (int64_t)r * bs + c)));
-  }
+  by_round(items, [&](auto count) {
+    constexpr int U = decltype(count)::value;  // items per thread with all their loads in flight
+    for (int q0 = threadIdx.x; q0 < items; q0 += kBlock * U) {
+      int t[U], c[U];
+#pragma unroll
+      for (int u = 0; u < U; u++) {
+        const int q = min(q0 + u * kBlock, items - 1);
+        t[u] = tl.t0 + (bs == 1 ? q : q / bs);
+        c[u] = bs == 1 ? 0 : q % bs;
+      }
+      int32_t r[U], l[U];
+      seg_roots<U>(sg, ridx, t, r);
+      seg_leaves<U>(sg, lidx, t, l);
+      T rv[U], lv[U];
+#pragma unroll
+      for (int u = 0; u < U; u++) {
+        rv[u] = ld(root + (int64_t)r[u] * bs + c[u]);
+        if (OP != OP_REPLACE) lv[u] = ld(leaf + (int64_t)l[u] * bs + c[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < U; u++)
+        if (q0 + u * kBlock < items)
+          st(leaf + (int64_t)l[u] * bs + c[u], OP == OP_REPLACE ? rv[u] : Op<OP, T>::apply(lv[u], rv[u]));
+    }
+  });
 }
 
 // ===================================================== Reduce: stream kinds
@@ -100,32 +120,31 @@ __global__ __launch_bounds__(kBlock) void k_reduce_plain(const DevSegment *__res
   const DevTile tl = tiles[blockIdx.x];
   const DevSegment sg = segs[tl.seg];
   const int items = (tl.t1 - tl.t0) * bs;
-  constexpr int U = 4;  // elements per thread with all their loads in flight
-  for (int q0 = threadIdx.x; q0 < items; q0 += kBlock * U) {
-    int64_t rq[U], lq[U];
+  by_round(items, [&](auto count) {
+    constexpr int U = decltype(count)::value;  // items per thread with all their loads in flight
+    for (int q0 = threadIdx.x; q0 < items; q0 += kBlock * U) {
+      int t[U], c[U];
 #pragma unroll
-    for (int u = 0; u < U; u++) {
-      const int q = q0 + u * kBlock;
-      rq[u] = -1;
-      if (q < items) {
-        const int lt = bs == 1 ? q : q / bs;
-        const int t = tl.t0 + lt;
-        const int c = q - lt * bs;
-        rq[u] = (int64_t)seg_root_s(sg, ridx, t) * bs + c;
-        lq[u] = (int64_t)seg_leaf_s(sg, lidx, t) * bs + c;
+      for (int u = 0; u < U; u++) {
+        const int q = min(q0 + u * kBlock, items - 1);
+        t[u] = tl.t0 + (bs == 1 ? q : q / bs);
+        c[u] = bs == 1 ? 0 : q % bs;
       }
+      int32_t r[U], l[U];
+      seg_roots<U>(sg, ridx, t, r);
+      seg_leaves<U>(sg, lidx, t, l);
+      T lv[U], rv[U];
+#pragma unroll
+      for (int u = 0; u < U; u++) {
+        lv[u] = ld_stream(leaf + (int64_t)l[u] * bs + c[u]);
+        if (OP != OP_REPLACE) rv[u] = ld(root + (int64_t)r[u] * bs + c[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < U; u++)
+        if (q0 + u * kBlock < items)
+          st(root + (int64_t)r[u] * bs + c[u], OP == OP_REPLACE ? lv[u] : Op<OP, T>::apply(rv[u], lv[u]));
     }
-    T lv[U], rv[U];
-#pragma unroll
-    for (int u = 0; u < U; u++)
-      if (rq[u] >= 0) {
-        lv[u] = ld_stream(leaf + lq[u]);
-        rv[u] = ld(root + rq[u]);
-      }
-#pragma unroll
-    for (int u = 0; u < U; u++)
-      if (rq[u] >= 0) st(root + rq[u], Op<OP, T>::apply(rv[u], lv[u]));
-  }
+  });
 }
 
 // The same on an SF whose roots have at most one leaf each and whose root
@@ -144,31 +163,31 @@ __global__ __launch_bounds__(kBlock) void k_reduce_rooted(const int32_t *__restr
   const int w = bs / NV;
   const int t0 = blockIdx.x * per;
   const int items = min(per, nroots - t0) * w;
-  constexpr int U = 4;  // elements per thread with all their loads in flight
-  for (int q0 = threadIdx.x; q0 < items; q0 += kBlock * U) {
-    int64_t rq[U], lq[U];
+  by_round(items, [&](auto count) {
+    constexpr int U = decltype(count)::value;  // items per thread with all their loads in flight
+    for (int q0 = threadIdx.x; q0 < items; q0 += kBlock * U) {
+      int32_t r[U], l[U];
+      int c[U];
 #pragma unroll
-    for (int u = 0; u < U; u++) {
-      const int q = q0 + u * kBlock;
-      rq[u] = -1;
-      if (q < items) {
+      for (int u = 0; u < U; u++) {
+        const int q = min(q0 + u * kBlock, items - 1);
         const int lt = w == 1 ? q : q / w;
-        const int c = (q - lt * w) * NV;
-        rq[u] = (int64_t)ld_stream(troot + t0 + lt) * bs + c;
-        lq[u] = (int64_t)ld_stream(sl + t0 + lt) * bs + c;
+        c[u] = (q - lt * w) * NV;
+        r[u] = ld_stream(troot + t0 + lt);
+        l[u] = ld_stream(sl + t0 + lt);
       }
+      Vec<T, NV> lv[U], rv[U];
+#pragma unroll
+      for (int u = 0; u < U; u++) {
+        lv[u] = vld<T, NV>(leaf + (int64_t)l[u] * bs + c[u]);
+        if (OP != OP_REPLACE) rv[u] = vld<T, NV>(root + (int64_t)r[u] * bs + c[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < U; u++)
+        if (q0 + u * kBlock < items)
+          vst<T, NV>(root + (int64_t)r[u] * bs + c[u], OP == OP_REPLACE ? lv[u] : vop<OP, T, NV>(rv[u], lv[u]));
     }
-    Vec<T, NV> lv[U], rv[U];
-#pragma unroll
-    for (int u = 0; u < U; u++)
-      if (rq[u] >= 0) {
-        lv[u] = vld<T, NV>(leaf + lq[u]);
-        if (OP != OP_REPLACE) rv[u] = vld<T, NV>(root + rq[u]);
-      }
-#pragma unroll
-    for (int u = 0; u < U; u++)
-      if (rq[u] >= 0) vst<T, NV>(root + rq[u], OP == OP_REPLACE ? lv[u] : vop<OP, T, NV>(rv[u], lv[u]));
-  }
+  });
 }
 
 // Atomic reduction over a persistent grid.  Roots encoded as -(h+1) in
@@ -194,23 +213,21 @@ __global__ __launch_bounds__(kBlock) void k_reduce_atomic(const DevSegment *__re
     constexpr int U = 4;
     for (int q0 = threadIdx.x; q0 < items; q0 += kBlock * U) {
       T v[U];
-      int32_t rr[U];
-      int cc[U];
+      int32_t rr[U], l[U];
+      int t[U], cc[U];
 #pragma unroll
       for (int u = 0; u < U; u++) {
-        const int q = q0 + u * kBlock;
-        rr[u] = INT32_MIN;
-        if (q < items) {
-          const int t = tl.t0 + q / bs;
-          cc[u] = q % bs;
-          rr[u] = seg_root(sg, ridx, t);
-          const int32_t l = seg_leaf(sg, lidx, t);
-          v[u] = leaf[(int64_t)l * bs + cc[u]];
-        }
+        const int q = min(q0 + u * kBlock, items - 1);
+        t[u] = tl.t0 + q / bs;
+        cc[u] = q % bs;
       }
+      seg_roots<U>(sg, ridx, t, rr);
+      seg_leaves<U>(sg, lidx, t, l);
+#pragma unroll
+      for (int u = 0; u < U; u++) v[u] = leaf[(int64_t)l[u] * bs + cc[u]];
 #pragma unroll
       for (int u = 0; u < U; u++) {
-        if (rr[u] == INT32_MIN) continue;
+        if (q0 + u * kBlock >= items) continue;
         if (rr[u] >= 0) {
           AtomicG<OP, T>::run(root + (int64_t)rr[u] * bs + cc[u], v[u]);
         } else {
@@ -347,32 +364,29 @@ __global__ __launch_bounds__(kBlock) void k_reduce_split(const DevSegment *__res
     const int items = (tl.t1 - tl.t0) * bs;
     constexpr int U = 4;  // elements per thread with all their loads in flight
     for (int q0 = threadIdx.x; q0 < items; q0 += kBlock * U) {
-      int64_t rq[U], lq[U];
+      int t[U], c[U];
+      bool ok[U];  // in the tile, and a single-leaf root's
 #pragma unroll
       for (int u = 0; u < U; u++) {
-        const int q = q0 + u * kBlock;
-        rq[u] = -1;
-        if (q < items) {
-          const int lt = bs == 1 ? q : q / bs;
-          const int t = tl.t0 + lt;
-          const int c = q - lt * bs;
-          const int p = sg.pbase + t;
-          if (!((rep_bits[p >> 5] >> (p & 31)) & 1u)) {
-            rq[u] = (int64_t)seg_root_s(sg, ridx, t) * bs + c;
-            lq[u] = (int64_t)seg_leaf_s(sg, lidx, t) * bs + c;
-          }
-        }
+        const int q = min(q0 + u * kBlock, items - 1);
+        const int lt = bs == 1 ? q : q / bs;
+        t[u] = tl.t0 + lt;
+        c[u] = q - lt * bs;
+        const int p = sg.pbase + t[u];
+        ok[u] = q0 + u * kBlock < items && !((rep_bits[p >> 5] >> (p & 31)) & 1u);
       }
+      int32_t r[U], l[U];
+      seg_roots<U>(sg, ridx, t, r);
+      seg_leaves<U>(sg, lidx, t, l);
       T lv[U], rv[U];
 #pragma unroll
-      for (int u = 0; u < U; u++)
-        if (rq[u] >= 0) {
-          lv[u] = ld_stream(leaf + lq[u]);
-          rv[u] = ld(root + rq[u]);
-        }
+      for (int u = 0; u < U; u++) {
+        lv[u] = ld_stream(leaf + (int64_t)l[u] * bs + c[u]);
+        rv[u] = ld(root + (int64_t)r[u] * bs + c[u]);
+      }
 #pragma unroll
       for (int u = 0; u < U; u++)
-        if (rq[u] >= 0) st(root + rq[u], Op<OP, T>::apply(rv[u], lv[u]));
+        if (ok[u]) st(root + (int64_t)r[u] * bs + c[u], Op<OP, T>::apply(rv[u], lv[u]));
     }
     return;
   }
@@ -420,12 +434,27 @@ __global__ __launch_bounds__(kBlock) void k_fop_atomic(const DevSegment *__restr
   const DevTile tl = tiles[blockIdx.x];
   const DevSegment sg = segs[tl.seg];
   const int items = (tl.t1 - tl.t0) * bs;
-  for (int q = threadIdx.x; q < items; q += kBlock) {
-    const int t = tl.t0 + q / bs;
-    const int c = q % bs;
-    const int32_t r = seg_root(sg, ridx, t);
-    const int64_t l = (int64_t)seg_leaf(sg, lidx, t) * bs + c;
-    upd[l] = fetch_add_g(root + (int64_t)r * bs + c, leaf[l]);
+  constexpr int U = 4;  // returning atomics in flight per thread
+  for (int q0 = threadIdx.x; q0 < items; q0 += kBlock * U) {
+    int t[U], c[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const int q = min(q0 + u * kBlock, items - 1);
+      t[u] = tl.t0 + q / bs;
+      c[u] = q % bs;
+    }
+    int32_t r[U], l[U];
+    seg_roots<U>(sg, ridx, t, r);
+    seg_leaves<U>(sg, lidx, t, l);
+    T v[U], got[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) v[u] = leaf[(int64_t)l[u] * bs + c[u]];
+#pragma unroll
+    for (int u = 0; u < U; u++)
+      if (q0 + u * kBlock < items) got[u] = fetch_add_g(root + (int64_t)r[u] * bs + c[u], v[u]);
+#pragma unroll
+    for (int u = 0; u < U; u++)
+      if (q0 + u * kBlock < items) upd[(int64_t)l[u] * bs + c[u]] = got[u];
   }
 }
 
@@ -609,7 +638,8 @@ static int check_launch() {
 template <typename Word>
 static void bcast_move_w(sf_s *sf, int W, const void *root, void *leaf, hipStream_t st) {
   const DevPlan &d = sf->dp;
-  const int sh = sf->hp.tile_leaves >= kTileLeaves ? 1 : 0;  // two blocks per full-size tile
+  // blocks per full-size tile: about four words per thread of a block
+  const int sh = sf->hp.tile_leaves < kTileLeaves || W == 1 ? 0 : (W < 4 ? 1 : 2);
   const unsigned g = (unsigned)sf->hp.tiles.size() << sh;
   const Word *r = (const Word *)root;
   Word *l = (Word *)leaf;
