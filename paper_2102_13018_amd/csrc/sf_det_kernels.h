@@ -55,6 +55,87 @@ __global__ __launch_bounds__(kBlock) void k_det_chunk(const DevChunk *__restrict
   }
 }
 
+// The canonical pairwise tree of the n <= kChunk values load(0) .. load(n - 1)
+// over a wavefront, as in k_det_chunk; the result is in lane 0.
+template <typename T, int OP, typename Load>
+__device__ __forceinline__ T wave_chunk_tree(int lane, int n, Load load) {
+  constexpr int LPT = kChunkLPT;
+  const int m = n - lane * LPT;
+  T x[LPT];
+#pragma unroll
+  for (int s = 0; s < LPT; s++) x[s] = load(min(lane * LPT + s, n - 1));
+#pragma unroll
+  for (int d = 1; d < LPT; d *= 2)
+#pragma unroll
+    for (int p = 0; p + d < LPT; p += 2 * d)
+      if (p + d < m) x[p] = Op<OP, T>::apply(x[p], x[p + d]);
+  T v = x[0];
+#pragma unroll
+  for (int d = 1; d < 64; d *= 2) {
+    const T o = shfl_down(v, d);
+    if ((lane & (2 * d - 1)) == 0 && (lane + d) * LPT < n) v = Op<OP, T>::apply(v, o);
+  }
+  return v;
+}
+
+// Every level above level 0 in one launch: a wavefront per root of at most
+// kChunk level-0 results, a block per root of more (at most kChunk * kChunk),
+// whose wavefronts take its level-1 chunks and leave their results in the LDS
+// for the last tree.  The chunk boundaries and trees are those of k_det_chunk
+// level by level.  Bound by the latency of its few dependent loads, which is
+// why one launch replaces one per level: 1.2M Zipf leaves of f32 2.1 + 3.0 ->
+// 3.5 us (the Reduce 22.3 -> 19.2), MAXLOC of 2M 35.4 -> 32.5, 16M f64 4.6 +
+// 4.8 -> 4.9 (123.3 -> 120.8).  Blocks of 16 wavefronts, so that the level-1
+// chunks of the hottest root (30 at 16M leaves) take two rounds.
+constexpr int kLevelThreads = 1024;
+template <typename T, int OP>
+__global__ __launch_bounds__(kLevelThreads) void k_det_levels(const DevChunk *__restrict__ tops, int nbig, int ntops,
+                                                              const T *__restrict__ seq, T *__restrict__ root, int bs) {
+  constexpr int kWaves = kLevelThreads / 64;
+  __shared__ __align__(16) unsigned char raw[kChunk * sizeof(T)];
+  T *part = reinterpret_cast<T *>(raw);
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const bool big = (int)blockIdx.x < nbig;
+  const int i = big ? (int)blockIdx.x : nbig + ((int)blockIdx.x - nbig) * kWaves + wv;
+  if (!big) {
+    if (i >= ntops) return;
+    const DevChunk ch = tops[i];
+    for (int c = 0; c < bs; c++) {
+      T *rp = root + (int64_t)ch.dst * bs + c;
+      const T r = ld(rp);
+      const T v = wave_chunk_tree<T, OP>(lane, ch.n, [&](int e) { return ld(seq + (int64_t)(ch.src + e) * bs + c); });
+      if (lane == 0) st(rp, Op<OP, T>::apply(r, v));
+    }
+    return;
+  }
+  const DevChunk ch = tops[i];
+  const int nc = (ch.n + kChunk - 1) / kChunk;
+  for (int c = 0; c < bs; c++) {
+    T *rp = root + (int64_t)ch.dst * bs + c;
+    const T r = ld(rp);
+    for (int j = wv; j < nc; j += kWaves) {
+      const int64_t e0 = (int64_t)ch.src + j * kChunk;
+      const T v = wave_chunk_tree<T, OP>(lane, min(kChunk, ch.n - j * kChunk),
+                                         [&](int e) { return ld(seq + (e0 + e) * bs + c); });
+      if (lane == 0) st(part + j, v);
+    }
+    __syncthreads();
+    if (wv == 0) {
+      const T v = wave_chunk_tree<T, OP>(lane, nc, [&](int e) { return ld(part + e); });
+      if (lane == 0) st(rp, Op<OP, T>::apply(r, v));
+    }
+    __syncthreads();
+  }
+}
+template <typename T, int OP>
+void launch_levels(const sf_s *sf, const T *seq, T *root, int bs, hipStream_t st) {
+  const int n = (int)sf->hp.tops.size(), nbig = sf->hp.ntops_big;
+  constexpr int kWaves = kLevelThreads / 64;
+  if (n == 0) return;
+  hipLaunchKernelGGL((k_det_levels<T, OP>), dim3((unsigned)(nbig + (n - nbig + kWaves - 1) / kWaves)),
+                     dim3(kLevelThreads), 0, st, sf->dp.tops, nbig, n, seq, root, bs);
+}
+
 // Large roots, pass 2: one wavefront per large root turns its chunk sums
 // into chunk bases (root value + exclusive prefix) and writes the final
 // root.  Each iteration scans 64*kScanPer chunk sums: kScanPer consecutive

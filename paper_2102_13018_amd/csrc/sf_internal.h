@@ -132,6 +132,12 @@ struct HostPlan {
   std::vector<int32_t> small_all; // the degree classes concatenated, class by class
   std::vector<ChunkLevel> levels; // chunk levels of the large roots
   int64_t scratch_len = 0;        // max sequence length written by a chunk level
+  // roots with several level-0 results ({first, count, root} in level 0's
+  // output): those of more than kChunk results first (ntops_big of them).
+  // Empty when some root has more than kChunk * kChunk results (its levels
+  // take a launch each).
+  std::vector<DevChunk> tops;
+  int32_t ntops_big = 0;
   // Reduce split for SFs whose repeated roots all have at most kSmallMaxDeg
   // leaves and hold under half of the leaves: the leaves of single-leaf roots
   // stream (index or pattern) and update their roots plainly, the repeated
@@ -209,6 +215,7 @@ struct DevPlan {
   int32_t *large = nullptr;
   int32_t *small_all = nullptr;
   std::vector<DevChunk *> levels;
+  DevChunk *tops = nullptr;
   DevChunk *fo_chunks = nullptr;
   int32_t *fo_root_first = nullptr;
   struct Stage {

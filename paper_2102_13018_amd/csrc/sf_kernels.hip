@@ -804,13 +804,16 @@ static int reduce_det_t(sf_s *sf, const T *leaf, T *root, int bs, hipStream_t st
   }
   // chunk levels
   if (!h.levels.empty()) {
-    for (size_t k = 0; k < h.levels.size(); k++) {
+    // level 0, then the levels above it in one launch where the plan allows
+    const size_t nlev = h.tops.empty() ? h.levels.size() : 1;
+    for (size_t k = 0; k < nlev; k++) {
       const int nch = (int)h.levels[k].chunks.size();
       const T *src = k == 0 ? leaf : buf[(k - 1) % 2];
       const int32_t *sl = k == 0 ? d.sl : nullptr;
       hipLaunchKernelGGL((k_det_chunk<T, OP>), dim3(nblocks((int64_t)nch * 64)), dim3(kBlock), 0, st, d.levels[k], nch,
                          sl, src, buf[k % 2], root, bs);
     }
+    launch_levels<T, OP>(sf, (const T *)buf[0], root, bs, st);
   }
   return check_launch();
 }

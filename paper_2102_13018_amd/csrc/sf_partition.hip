@@ -1153,7 +1153,12 @@ int launch_reduce_part(sf_s *sf, const T *leaf, T *root, int bs, bool atomic, hi
   if (rc) return rc;
   const unsigned gw = (unsigned)hs.win.size();
   if constexpr (kHasAtomic<OP>) {
-    if (atomic) {
+    // chunk results of a root meet in the root itself, in arrival order, also
+    // in deterministic mode where the order cannot show (a maximum or minimum
+    // under the total order of the keys, which the integer atomics follow, and
+    // wrapping sums): no chunk levels (1.2M Zipf leaves of f64: a sum with
+    // levels 26.7 us, a maximum without 22.2)
+    if (atomic || OrderFree<T, OP>::value) {
       rc = sp_reduce_launch<T, OP, true>(gw, pl, st, ds.win, ds.sroot, ds.wchunk, ds.lpos, (const T *)scr,
                                          buf[0], root, bs);
       if (rc) return rc;
@@ -1163,6 +1168,10 @@ int launch_reduce_part(sf_s *sf, const T *leaf, T *root, int bs, bool atomic, hi
   rc = sp_reduce_launch<T, OP, false>(gw, pl, st, ds.win, ds.sroot, ds.wchunk, ds.lpos, (const T *)scr, buf[0],
                                       root, bs);
   if (rc) return rc;
+  if (!h.tops.empty()) {
+    launch_levels<T, OP>(sf, (const T *)buf[0], root, bs, st);
+    return sp_check();
+  }
   for (size_t k = 1; k < h.levels.size(); k++) {
     const int nch = (int)h.levels[k].chunks.size();
     hipLaunchKernelGGL((k_det_chunk<T, OP>), dim3((unsigned)((nch * 64 + kBlock - 1) / kBlock)), dim3(kBlock), 0, st,

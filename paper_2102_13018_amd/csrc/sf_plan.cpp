@@ -630,6 +630,17 @@ int analyze(sf_s *sf) {
       next.push_back({p.root, base, nc});
     }
     hp.scratch_len = std::max(hp.scratch_len, lv.out_len);
+    if (hp.levels.empty()) {
+      for (const bool big : {true, false})
+        for (const Pend &p : next)
+          if ((p.n > kChunk) == big) {
+            hp.tops.push_back({p.src, p.n, p.root, 0});
+            hp.ntops_big += big ? 1 : 0;
+          }
+      for (const Pend &p : next)
+        if (p.n > kChunk * kChunk) hp.tops.clear();
+      if (hp.tops.empty()) hp.ntops_big = 0;
+    }
     hp.levels.push_back(std::move(lv));
     cur.swap(next);
   }
@@ -844,6 +855,7 @@ int upload(sf_s *sf) {
   dp.levels.assign(hp.levels.size(), nullptr);
   for (size_t k = 0; k < hp.levels.size(); k++)
     add(hp.levels[k].chunks.data(), hp.levels[k].chunks.size() * sizeof(DevChunk), (void **)&dp.levels[k]);
+  add(hp.tops.data(), hp.tops.size() * sizeof(DevChunk), (void **)&dp.tops);
   add(hp.fo_chunks.data(), hp.fo_chunks.size() * sizeof(DevChunk), (void **)&dp.fo_chunks);
   add(hp.fo_root_first.data(), hp.fo_root_first.size() * 4, (void **)&dp.fo_root_first);
   for (int c = 0; c < 2; c++) {
