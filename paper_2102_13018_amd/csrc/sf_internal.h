@@ -43,6 +43,17 @@ constexpr int kStageMaxLds = 131072;     // LDS of one staged block (bytes)
 constexpr int64_t kPartitionPlan = 1 << 16;
 constexpr int64_t kPartitionMid = 1 << 19;
 constexpr int64_t kPartitionBig = 1 << 20;
+// Bcast through a copy of the touched roots by decreasing degree (units of at
+// most 16 bytes): for SFs of at least kCompactLeaves leaves and 8 leaves per
+// touched root whose quarter of the roots of highest degree holds at least
+// 60% of the leaves, when the root array is at least kCompactRootBytes (half
+// again an XCD's L2).  Random roots of a popular few then share lines: Zipf
+// 1.1, 2M roots, 16M leaves of f64 86 -> 62 us plus 9 for the copy, f32 70 ->
+// 42 + 6; 1M roots, 8M leaves, Zipf 1.3 32 -> 23 + 3; Zipf 0.8, 2M roots, 16M
+// leaves 172 -> 118 + 18.  At 6 leaves per root (4M, Zipf 0.9) the copy cost
+// what it gained, and equal degrees gain nothing.
+constexpr int64_t kCompactLeaves = 1 << 21;
+constexpr int64_t kCompactRootBytes = 6 << 20;
 // Hot roots of the partitioned path: at least this many leaves per pass-A
 // tile on average (fewer and a group costs about what the windows cost),
 // and at most kHotRootsMax of them.
@@ -117,6 +128,9 @@ struct HostPlan {
   std::vector<DevTile> tiles;
   int32_t tile_leaves = kTileLeaves;  // leaves per tile of this SF
   bool all_contig = false;            // every segment contiguous on both sides (few segments)
+  // Bcast through degree-ordered roots (empty: not taken)
+  std::vector<int32_t> corder;    // touched roots by decreasing degree, ascending in a degree
+  std::vector<int32_t> cidx;      // place of the root of each processed leaf in corder (as ridx)
   bool rooted = false;                // Reduce walks the (single-leaf) roots in ascending order
   std::vector<int32_t> ridx;      // root index per processed leaf (generic root sides)
   std::vector<int32_t> ridx_hot;  // same, hot roots encoded as -(h+1)
@@ -209,6 +223,7 @@ struct DevPlan {
   size_t bytes = 0;
   DevSegment *segs = nullptr;
   DevTile *tiles = nullptr;
+  int32_t *corder = nullptr, *cidx = nullptr;
   int32_t *ridx = nullptr, *ridx_hot = nullptr, *lidx = nullptr, *hot_roots = nullptr;
   int32_t *troot = nullptr, *toff = nullptr, *sl = nullptr;
   int32_t *cls[kNumClasses] = {};
@@ -266,6 +281,13 @@ struct sf_s {
   void *scratch = nullptr;
   size_t scratch_bytes = 0;
   std::vector<void *> retired;
+  // degree-ordered copy of the roots for Bcast (allocated at set-up for 8-byte
+  // units), bound to the stream that first uses it; other streams and captures
+  // take the direct kernel
+  void *compact = nullptr;
+  size_t compact_bytes = 0;
+  bool compact_bound = false;
+  hipStream_t compact_stream = nullptr;
   // set only for the duration of an allocation-free call: scratch comes from
   // this fixed device buffer (one per device) and nothing is allocated
   void *fixed_scratch = nullptr;
@@ -294,6 +316,10 @@ inline bool scratch_fits(const sf_s *sf, size_t bytes) {
 // Device address and size of the calling device's fixed scratch buffer
 // (implemented in sf_noalloc.hip).
 int fixed_scratch(void **ptr, size_t *bytes);
+// The buffer of the degree-ordered roots for a Bcast on st, or nullptr when
+// that Bcast has to do without: another stream owns it, st is being captured
+// (a graph may be replayed beside eager calls), or there is no memory.
+void *compact_buffer(sf_s *sf, size_t bytes, hipStream_t st);
 
 // kernel launchers implemented in sf_kernels.hip
 int launch_bcast(sf_s *sf, sf_unit unit, const void *root, void *leaf, int op, hipStream_t st);

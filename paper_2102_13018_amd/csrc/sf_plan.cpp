@@ -654,6 +654,45 @@ int analyze(sf_s *sf) {
     hp.fo_root_first.push_back((int32_t)hp.fo_chunks.size());
   }
 
+  // ---- degree-ordered roots of Bcast, built beside the partition plans
+  std::thread compacting;
+  struct Join {
+    std::thread &t;
+    ~Join() {
+      if (t.joinable()) t.join();
+    }
+  } join_compacting{compacting};
+  if (L >= kCompactLeaves && (int64_t)hp.ridx.size() == L && T * 8 <= L && R * 16 >= kCompactRootBytes) {
+    auto compact = [&hp, T, L, R]() {
+      try {
+        constexpr int32_t kCap = 1 << 16;  // degrees from here on share a bucket
+        auto bucket = [&](int64_t t) { return std::min(hp.toff[t + 1] - hp.toff[t], kCap); };
+        std::vector<int32_t> first(kCap + 2, 0);  // [d]: roots of a degree above d
+        for (int64_t t = 0; t < T; t++) first[kCap - bucket(t) + 1]++;
+        for (int32_t b = 0; b <= kCap; b++) first[b + 1] += first[b];
+        std::vector<int32_t> order(T), place(R, 0);
+        int64_t quarter = 0;
+        for (int64_t t = 0; t < T; t++) {
+          const int32_t at = first[kCap - bucket(t)]++;
+          order[at] = hp.troot[t];
+          place[hp.troot[t]] = at;
+          if (at < T / 4) quarter += hp.toff[t + 1] - hp.toff[t];
+        }
+        if (quarter * 10 < L * 6) return;
+        std::vector<int32_t> idx(L);
+        for (int64_t p = 0; p < L; p++) idx[p] = place[hp.ridx[p]];
+        hp.cidx = std::move(idx);
+        hp.corder = std::move(order);
+      } catch (const std::bad_alloc &) {  // Bcast keeps the direct kernel
+      }
+    };
+    try {
+      compacting = std::thread(compact);
+    } catch (const std::system_error &) {  // no thread
+      compact();
+    }
+  }
+
   // ---- partitioned deterministic path
   const int pmode = sf->opts.partition;  // 0 auto, 1 on, 2 off
   if (sf->has_dup_roots && (pmode == 1 || (pmode == 0 && L >= kPartitionPlan))) {
@@ -774,6 +813,7 @@ int analyze(sf_s *sf) {
     hp.part_fop_atomic = pmode == 1 || L >= kPartitionBig;
   }
 
+  if (compacting.joinable()) compacting.join();
   for (auto &s : segs) std::vector<int64_t>().swap(s.members);  // only the sizes and patterns are kept
   sf->segments = std::move(segs);
   sf->hp = std::move(hp);
@@ -784,6 +824,11 @@ int analyze(sf_s *sf) {
 void free_device(sf_s *sf) {
   if (sf->dp.blob) (void)hipFree(sf->dp.blob);
   if (sf->scratch) (void)hipFree(sf->scratch);
+  if (sf->compact) (void)hipFree(sf->compact);
+  sf->compact = nullptr;
+  sf->compact_bytes = 0;
+  sf->compact_bound = false;
+  sf->compact_stream = nullptr;
   for (void *p : sf->retired) (void)hipFree(p);
   sf->retired.clear();
   sf->dp = DevPlan{};
@@ -817,6 +862,30 @@ int ensure_scratch(sf_s *sf, size_t bytes) {
   return SF_OK;
 }
 
+void *compact_buffer(sf_s *sf, size_t bytes, hipStream_t st) {
+  if (st == hipStreamPerThread) return nullptr;  // one handle, a stream per thread
+  if (sf->compact_bound && sf->compact_stream != st) return nullptr;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  if (cap != hipStreamCaptureStatusNone) return nullptr;
+  if (bytes > sf->compact_bytes) {
+    void *p = nullptr;
+    if (hipMalloc(&p, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    if (sf->compact) sf->retired.push_back(sf->compact);  // enqueued work may still use it
+    sf->compact = p;
+    sf->compact_bytes = bytes;
+  }
+  sf->compact_bound = true;
+  sf->compact_stream = st;
+  return sf->compact;
+}
+
 int acquire_scratch(sf_s *sf, size_t bytes, void **out) {
   if (sf->fixed_scratch) {
     if (bytes > sf->fixed_scratch_bytes) return SF_ERR_SCRATCH;
@@ -843,6 +912,8 @@ int upload(sf_s *sf) {
   add(hp.dsegs.data(), hp.dsegs.size() * sizeof(DevSegment), (void **)&dp.segs);
   add(hp.tiles.data(), hp.tiles.size() * sizeof(DevTile), (void **)&dp.tiles);
   add(hp.ridx.data(), hp.ridx.size() * 4, (void **)&dp.ridx);
+  add(hp.corder.data(), hp.corder.size() * 4, (void **)&dp.corder);
+  add(hp.cidx.data(), hp.cidx.size() * 4, (void **)&dp.cidx);
   add(hp.ridx_hot.data(), hp.ridx_hot.size() * 4, (void **)&dp.ridx_hot);
   add(hp.lidx.data(), hp.lidx.size() * 4, (void **)&dp.lidx);
   add(hp.hot_roots.data(), hp.hot_roots.size() * 4, (void **)&dp.hot_roots);
@@ -910,6 +981,15 @@ int upload(sf_s *sf) {
       return set_hip_error(e);
     }
     off += (p.bytes + 255) / 256 * 256;
+  }
+  if (!hp.corder.empty()) {  // not needed for a result: no error without it
+    const size_t bytes = hp.corder.size() * 8;
+    if (hipMalloc(&sf->compact, bytes) == hipSuccess) {
+      sf->compact_bytes = bytes;
+    } else {
+      sf->compact = nullptr;
+      (void)hipGetLastError();
+    }
   }
   return SF_OK;
 }
