@@ -939,6 +939,19 @@ __global__ __launch_bounds__(kStageThreads) __attribute__((amdgpu_waves_per_eu(8
     // 3: exclusive prefix inside each chunk plus the chunk's base
     chunk_apply(lds, cd, cv, nb, bs);
   }
+  if (ahead) {  // the places again, in flight across the barrier
+    int p[8];
+#pragma unroll
+    for (int u = 0; u < 8; u++) p[u] = lpos[win.base + min((int)threadIdx.x + u * kStageThreads, win.n - 1)];
+    __syncthreads();
+    T *dst = scr + win.base;
+#pragma unroll
+    for (int u = 0; u < 8; u++) {
+      const int q = threadIdx.x + u * kStageThreads;
+      if (q < win.n) dst[q] = lds[p[u] & 0x3fff];
+    }
+    return;
+  }
   __syncthreads();
   win_store(lds, scr, lpos, win, bs);
 }
