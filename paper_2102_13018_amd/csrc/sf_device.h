@@ -272,6 +272,13 @@ __device__ __forceinline__ int32_t seg_root(const DevSegment &s, const int32_t *
 __device__ __forceinline__ int32_t seg_leaf(const DevSegment &s, const int32_t *__restrict__ lidx, int32_t t) {
   return s.leaf.kind == SF_PATTERN_GENERIC ? lidx[s.loff + t] : pat_index(s.leaf, t);
 }
+// The same, for index arrays read once per operation (streaming loads).
+__device__ __forceinline__ int32_t seg_root_s(const DevSegment &s, const int32_t *__restrict__ ridx, int32_t t) {
+  return s.root.kind == SF_PATTERN_GENERIC ? ld_stream(ridx + s.roff + t) : pat_index(s.root, t);
+}
+__device__ __forceinline__ int32_t seg_leaf_s(const DevSegment &s, const int32_t *__restrict__ lidx, int32_t t) {
+  return s.leaf.kind == SF_PATTERN_GENERIC ? ld_stream(lidx + s.loff + t) : pat_index(s.leaf, t);
+}
 // The indices of U leaves of a segment side at once.  The side's kind is
 // looked at once and no load is conditional (callers clamp t into the tile),
 // so all U loads are in flight together: an index load inside a bounds check
@@ -571,10 +578,14 @@ __device__ __forceinline__ Vec<T, NV> vop(const Vec<T, NV> &a, const Vec<T, NV> 
 // combined at distances 8, 16, ... -- the same operands in the same order as
 // the tree over all D positions, with a fraction of its registers (which
 // keeps kernels with a 32-leaf class at a useful occupancy).  Positions past
-// the end load the last value again and are not combined: a conditional load
-// waits for the one before it, so a root of 5 to 8 leaves took up to four
-// round trips (64 items in one launch: 267 -> 250 us).
-template <int D, typename V, typename Load, typename Comb>
+// the end load the last value again and are not combined where ALL is set: a
+// conditional load waits for the one before it, so a root of 5 to 8 leaves
+// took up to four round trips (64 items in one launch: 267 -> 250 us).  The
+// kernels of one SF keep conditional loads: they run enough wavefronts to hide
+// the trips, and the extra loads and registers cost more than they give (256^3
+// halo Reduce: 7.2 us, 7.5 with ALL; units of four f64 13.4, 14.2; k-NN
+// graphs the same).
+template <int D, typename V, bool ALL = true, typename Load, typename Comb>
 __device__ __forceinline__ V pw_tree(int n, Load load, Comb comb) {
   constexpr int BMAX = sizeof(V) >= 16 ? 4 : 8;
   constexpr int B = D < BMAX ? D : BMAX;
@@ -587,7 +598,7 @@ __device__ __forceinline__ V pw_tree(int n, Load load, Comb comb) {
       V x[B];
 #pragma unroll
       for (int p = 0; p < B; p++)
-        x[p] = load(min(k * B + p, n - 1));
+        if (ALL || p < m) x[p] = load(ALL ? min(k * B + p, n - 1) : k * B + p);
 #pragma unroll
       for (int d = 1; d < B; d *= 2)
 #pragma unroll

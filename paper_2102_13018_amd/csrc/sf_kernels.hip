@@ -327,7 +327,7 @@ __global__ __launch_bounds__(kBlock) void k_maxloc_stream(const DevSegment *__re
 template <typename T, int OP, int NV, int D>
 __device__ __forceinline__ Vec<T, NV> small_tree_v(const int32_t *__restrict__ sl, const T *__restrict__ leaf, int g0,
                                                    int n, int bs, int c) {
-  return pw_tree<D, Vec<T, NV>>(
+  return pw_tree<D, Vec<T, NV>, false>(
       n, [&](int p) { return vld<T, NV>(leaf + (int64_t)sl[g0 + p] * bs + c); },
       [](const Vec<T, NV> &a, const Vec<T, NV> &b) { return vop<OP, T, NV>(a, b); });
 }
@@ -367,7 +367,11 @@ __global__ __launch_bounds__(kBlock) void k_det_small_all(const int32_t *__restr
 // processing position is marked in rep_bits belongs to a repeated root and
 // is skipped) and update those roots plainly; the remaining blocks give each
 // (repeated root, element) its register tree over the root's sorted leaves,
-// exactly as k_det_small_all.  The two parts write disjoint roots.
+// exactly as k_det_small_all.  The two parts write disjoint roots.  The loads
+// stay inside the condition here, unlike the other stream kernels': a tile
+// holds three items a thread or fewer of the short streams that take this
+// kernel, and the skipped and missing ones would cost loads of their own
+// (256^3 halo, bs 3, patterns: 11.2 us, 12.8 with unconditional loads).
 template <typename T, int OP>
 __global__ __launch_bounds__(kBlock) void k_reduce_split(const DevSegment *__restrict__ segs,
                                                          const DevTile *__restrict__ tiles, int ntiles,
@@ -385,29 +389,32 @@ __global__ __launch_bounds__(kBlock) void k_reduce_split(const DevSegment *__res
     const int items = (tl.t1 - tl.t0) * bs;
     constexpr int U = 4;  // elements per thread with all their loads in flight
     for (int q0 = threadIdx.x; q0 < items; q0 += kBlock * U) {
-      int t[U], c[U];
-      bool ok[U];  // in the tile, and a single-leaf root's
+      int64_t rq[U], lq[U];
 #pragma unroll
       for (int u = 0; u < U; u++) {
-        const int q = min(q0 + u * kBlock, items - 1);
-        const int lt = bs == 1 ? q : q / bs;
-        t[u] = tl.t0 + lt;
-        c[u] = q - lt * bs;
-        const int p = sg.pbase + t[u];
-        ok[u] = q0 + u * kBlock < items && !((rep_bits[p >> 5] >> (p & 31)) & 1u);
+        const int q = q0 + u * kBlock;
+        rq[u] = -1;
+        if (q < items) {
+          const int lt = bs == 1 ? q : q / bs;
+          const int t = tl.t0 + lt;
+          const int c = q - lt * bs;
+          const int p = sg.pbase + t;
+          if (!((rep_bits[p >> 5] >> (p & 31)) & 1u)) {
+            rq[u] = (int64_t)seg_root_s(sg, ridx, t) * bs + c;
+            lq[u] = (int64_t)seg_leaf_s(sg, lidx, t) * bs + c;
+          }
+        }
       }
-      int32_t r[U], l[U];
-      seg_roots<U>(sg, ridx, t, r);
-      seg_leaves<U>(sg, lidx, t, l);
       T lv[U], rv[U];
 #pragma unroll
-      for (int u = 0; u < U; u++) {
-        lv[u] = ld_stream(leaf + (int64_t)l[u] * bs + c[u]);
-        rv[u] = ld(root + (int64_t)r[u] * bs + c[u]);
-      }
+      for (int u = 0; u < U; u++)
+        if (rq[u] >= 0) {
+          lv[u] = ld_stream(leaf + lq[u]);
+          rv[u] = ld(root + rq[u]);
+        }
 #pragma unroll
       for (int u = 0; u < U; u++)
-        if (ok[u]) st(root + (int64_t)r[u] * bs + c[u], Op<OP, T>::apply(rv[u], lv[u]));
+        if (rq[u] >= 0) st(root + rq[u], Op<OP, T>::apply(rv[u], lv[u]));
     }
     return;
   }
@@ -659,8 +666,13 @@ static int check_launch() {
 template <typename Word>
 static void bcast_move_w(sf_s *sf, int W, const void *root, void *leaf, hipStream_t st) {
   const DevPlan &d = sf->dp;
-  // blocks per full-size tile: about four words per thread of a block
-  const int sh = sf->hp.tile_leaves < kTileLeaves || W == 1 ? 0 : (W < 4 ? 1 : 2);
+  // blocks per tile: about four words per thread of a block in full-size
+  // tiles.  Small tiles are split only where the root side is all patterns:
+  // with no index to wait for, more blocks serve better than more loads per
+  // thread (256^3 halo, 32-byte units: 6.4 us against 7.2 unsplit; 250K
+  // random roots, the same units: 5.3 split, 4.1 unsplit).
+  const bool small = sf->hp.tile_leaves < kTileLeaves;
+  const int sh = W == 1 || (small && !sf->hp.ridx.empty()) ? 0 : (W < 4 || small ? 1 : 2);
   const unsigned g = (unsigned)sf->hp.tiles.size() << sh;
   const Word *r = (const Word *)root;
   Word *l = (Word *)leaf;
