@@ -214,15 +214,15 @@ def build_spmv_ops(torch, S, inputs, g):
     r8 = lambda u: L * u + 2 * Rt * u + idx        # Reduce
     f8 = lambda u: 2 * L * u + 2 * Rt * u + idx    # FetchAndOp
     ops = [
-        Op("bcast_replace_f64", lambda: sf.bcast(xr64, yl64, "replace", unit=u64), b8(8), "k_bcast_move"),
+        Op("bcast_replace_f64", lambda: sf.bcast(xr64, yl64, "replace", unit=u64), b8(8), "k_order_roots + k_bcast_move"),
         Op("reduce_sum_f64_atomic", red("atomic", xl64, xr64, "sum", u64), r8(8), "k_sp_move + k_sp_reduce<atomic>"),
         Op("reduce_sum_f64_det", red("deterministic", xl64, xr64, "sum", u64), r8(8),
-           "k_sp_move + k_sp_reduce + k_det_chunk"),
+           "k_sp_move + k_sp_reduce + k_det_levels"),
         Op("reduce_sum_f32_det", red("deterministic", xl32, xr32, "sum", u32), r8(4),
-           "k_sp_move + k_sp_reduce + k_det_chunk"),
+           "k_sp_move + k_sp_reduce + k_det_levels"),
         Op("reduce_max_f64_atomic", red("atomic", xl64, xr64, "max", u64), r8(8), "k_sp_move + k_sp_reduce<atomic>"),
         Op("reduce_maxloc_det", red("deterministic", lpair, rpair, "maxloc", upair), r8(16),
-           "k_sp_move + k_sp_reduce + k_det_chunk"),
+           "k_sp_move + k_sp_reduce + k_det_levels"),
         Op("fetch_and_op_i64_det", fop("deterministic"), f8(8),
            "k_sp_move + k_sp_fop<det> + k_sp_span_scan + k_sp_move<add bases>"),
         Op("fetch_and_op_i64_atomic", fop("atomic"), f8(8), "k_sp_move + k_sp_fop<atomic> + k_sp_move"),
