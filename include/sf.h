@@ -433,6 +433,16 @@ int sf_batch_destroy(sf_batch_t *batch);
 int sf_get_info(sf_t sf, sf_info *info);
 /* Segment s (0 <= s < nsegments) after sf_setup. */
 int sf_get_segment(sf_t sf, int64_t s, sf_segment_info *seg);
+/* Which of its kernels an SF takes, decided by sf_setup from sizes, degrees
+ * and index orders (for tests and measurements; results do not depend on it). */
+typedef struct {
+  int64_t degree_ordered;    /* touched roots that a one-word Bcast REPLACE copies by decreasing degree (0: none) */
+  int32_t last_bcast_copied; /* 1: the last Bcast REPLACE gathered from that copy */
+  int32_t rooted;            /* 1: Reduce walks the single-leaf roots in ascending order */
+  int32_t slot_ordered;      /* segments whose leaves are walked in slot order */
+  int32_t level_roots;       /* roots whose chunk levels above level 0 share a launch (0: a launch per level) */
+} sf_choices;
+int sf_get_choices(sf_t sf, sf_choices *choices);
 const char *sf_error_string(int code);
 /* The HIP error behind the last SF_ERR_HIP of the calling thread. */
 int sf_last_hip_error(void);

@@ -317,6 +317,19 @@ extern "C" int sf_get_info(sf_t sf, sf_info *info) {
   return SF_OK;
 }
 
+extern "C" int sf_get_choices(sf_t sf, sf_choices *choices) {
+  if (!sf || !choices) return SF_ERR_ARG;
+  std::lock_guard<std::mutex> g(sf->mu);
+  std::memset(choices, 0, sizeof(*choices));
+  if (!sf->analyzed) return SF_ERR_NOT_SETUP;
+  choices->degree_ordered = (int64_t)sf->hp.corder.size();
+  choices->last_bcast_copied = sf->last_bcast_copied ? 1 : 0;
+  choices->rooted = sf->hp.rooted ? 1 : 0;
+  choices->slot_ordered = sf->hp.slot_ordered;
+  choices->level_roots = (int32_t)sf->hp.tops.size();
+  return SF_OK;
+}
+
 extern "C" int sf_get_segment(sf_t sf, int64_t s, sf_segment_info *seg) {
   if (!sf || !seg) return SF_ERR_ARG;
   std::lock_guard<std::mutex> g(sf->mu);

@@ -132,6 +132,7 @@ struct HostPlan {
   std::vector<int32_t> corder;    // touched roots by decreasing degree, ascending in a degree
   std::vector<int32_t> cidx;      // place of the root of each processed leaf in corder (as ridx)
   bool rooted = false;                // Reduce walks the (single-leaf) roots in ascending order
+  int32_t slot_ordered = 0;           // segments walked in slot order
   std::vector<int32_t> ridx;      // root index per processed leaf (generic root sides)
   std::vector<int32_t> ridx_hot;  // same, hot roots encoded as -(h+1)
   std::vector<int32_t> lidx;      // leaf slot per processed leaf (generic leaf sides)
@@ -288,6 +289,7 @@ struct sf_s {
   size_t compact_bytes = 0;
   bool compact_bound = false;
   hipStream_t compact_stream = nullptr;
+  bool last_bcast_copied = false;  // the last Bcast REPLACE gathered from it
   // set only for the duration of an allocation-free call: scratch comes from
   // this fixed device buffer (one per device) and nothing is allocated
   void *fixed_scratch = nullptr;

@@ -475,6 +475,7 @@ int analyze(sf_s *sf) {
       } else {
         to_sort.clear();
       }
+      hp.slot_ordered = (int32_t)to_sort.size();
       for (int32_t k : to_sort) lay[k].slots.resize(lay[k].members.size());
       if (!to_sort.empty())
         for (int64_t l = 0; l < sf->leafspace; l++) {

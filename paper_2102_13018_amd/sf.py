@@ -37,7 +37,7 @@ EXPORTS = [
     "sf_get_graph", "sf_create_embedded_root_sf", "sf_create_embedded_leaf_sf", "sf_compose", "sf_compose_inverse",
     "sf_batch_create", "sf_batch_launch", "sf_batch_launch_separate", "sf_batch_graph_capture",
     "sf_batch_graph_launch", "sf_batch_autotune", "sf_batch_get_config", "sf_batch_set_config",
-    "sf_batch_destroy", "sf_get_info", "sf_get_segment", "sf_error_string", "sf_last_hip_error",
+    "sf_batch_destroy", "sf_get_info", "sf_get_choices", "sf_get_segment", "sf_error_string", "sf_last_hip_error",
     "sf_destroy",
 ]
 
@@ -90,6 +90,11 @@ class SfInfo(ctypes.Structure):
                 ("device_bytes", ctypes.c_int64), ("hot_roots", ctypes.c_int64)]
 
 
+class SfChoices(ctypes.Structure):
+    _fields_ = [("degree_ordered", ctypes.c_int64), ("last_bcast_copied", ctypes.c_int32),
+                ("rooted", ctypes.c_int32), ("slot_ordered", ctypes.c_int32), ("level_roots", ctypes.c_int32)]
+
+
 class SfBatchItem(ctypes.Structure):
     _fields_ = [("sf", ctypes.c_void_p), ("unit", SfUnit), ("kind", ctypes.c_int32),
                 ("op", ctypes.c_int32), ("rootdata", ctypes.c_void_p), ("leafdata", ctypes.c_void_p),
@@ -139,6 +144,7 @@ def lib():
         L.sf_batch_set_config.argtypes = [p, i32, i32]
         L.sf_batch_destroy.argtypes = [ctypes.POINTER(p)]
         L.sf_get_info.argtypes = [p, ctypes.POINTER(SfInfo)]
+        L.sf_get_choices.argtypes = [p, ctypes.POINTER(SfChoices)]
         L.sf_get_segment.argtypes = [p, i64, ctypes.POINTER(SfSegmentInfo)]
         L.sf_error_string.argtypes = [ctypes.c_int]
         L.sf_error_string.restype = ctypes.c_char_p
@@ -432,6 +438,11 @@ class StarForest:
         inf = SfInfo()
         check(lib().sf_get_info(self.h, ctypes.byref(inf)), "sf_get_info")
         return {f: getattr(inf, f) for f, _ in inf._fields_}
+
+    def choices(self):
+        c = SfChoices()
+        check(lib().sf_get_choices(self.h, ctypes.byref(c)), "sf_get_choices")
+        return {f: getattr(c, f) for f, _ in c._fields_}
 
     def segment(self, s):
         seg = SfSegmentInfo()
