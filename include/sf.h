@@ -33,6 +33,13 @@
  *    sf_destroy.  So calls may be captured into a HIP graph once the same
  *    calls have run eagerly (capture allocates nothing), and such graphs
  *    stay valid until the SF is set up again or destroyed.
+ *  - A one-word Bcast REPLACE of a large SF with popular roots gathers from a
+ *    copy of its roots, in one of two buffers (16 bytes per touched root each,
+ *    allocated by sf_setup and part of sf_info.device_bytes).  A buffer belongs
+ *    to the stream that used it last until its calls have completed; calls on
+ *    a third stream before that, and captured calls, gather from rootdata: the
+ *    same result, slower.  A stream that used one once, or more than 4 times,
+ *    hands it on with its next call after a third stream has asked.
  *  - sf_setup uploads the plan to the current device; *_begin returns
  *    SF_ERR_ARG when called with another device current.
  */

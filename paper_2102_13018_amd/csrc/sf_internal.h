@@ -282,14 +282,20 @@ struct sf_s {
   void *scratch = nullptr;
   size_t scratch_bytes = 0;
   std::vector<void *> retired;
-  // degree-ordered copy of the roots for Bcast (allocated at set-up for 8-byte
-  // units), bound to the stream that first uses it; other streams and captures
-  // take the direct kernel
-  void *compact = nullptr;
-  size_t compact_bytes = 0;
-  bool compact_bound = false;
-  hipStream_t compact_stream = nullptr;
-  bool last_bcast_copied = false;  // the last Bcast REPLACE gathered from it
+  // Two buffers for the degree-ordered copy of the roots (16 bytes per touched
+  // root each, allocated at set-up).  The stream of the last Bcast that used
+  // one owns it; another stream gets it once an event behind that Bcast has
+  // completed.  Behind which Bcasts one is recorded: compact_done.
+  struct Compact {
+    void *buf = nullptr;
+    hipEvent_t ev = nullptr;
+    hipStream_t stream = nullptr;  // the owner (uses > 0)
+    int64_t uses = 0;              // Bcasts of the owner
+    bool marked = false;           // ev is behind the last of them
+    bool wanted = false;           // another stream has asked since
+  } compact[2];
+  size_t compact_bytes = 0;        // of each
+  bool last_bcast_copied = false;  // the last Bcast REPLACE gathered from one
   // set only for the duration of an allocation-free call: scratch comes from
   // this fixed device buffer (one per device) and nothing is allocated
   void *fixed_scratch = nullptr;
@@ -318,10 +324,12 @@ inline bool scratch_fits(const sf_s *sf, size_t bytes) {
 // Device address and size of the calling device's fixed scratch buffer
 // (implemented in sf_noalloc.hip).
 int fixed_scratch(void **ptr, size_t *bytes);
-// The buffer of the degree-ordered roots for a Bcast on st, or nullptr when
-// that Bcast has to do without: another stream owns it, st is being captured
-// (a graph may be replayed beside eager calls), or there is no memory.
-void *compact_buffer(sf_s *sf, size_t bytes, hipStream_t st);
+// A buffer of the degree-ordered roots for a Bcast on st, or nullptr when that
+// Bcast has to do without: other streams' Bcasts may still read both, st is
+// being captured (a graph may be replayed beside eager calls), or there is no
+// memory.  compact_done follows the Bcast's last kernel.
+sf_s::Compact *compact_buffer(sf_s *sf, size_t bytes, hipStream_t st);
+void compact_done(sf_s::Compact *c, hipStream_t st);
 
 // kernel launchers implemented in sf_kernels.hip
 int launch_bcast(sf_s *sf, sf_unit unit, const void *root, void *leaf, int op, hipStream_t st);

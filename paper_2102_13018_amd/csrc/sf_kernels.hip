@@ -677,14 +677,14 @@ static void bcast_move_w(sf_s *sf, int W, const void *root, void *leaf, hipStrea
   const Word *r = (const Word *)root;
   Word *l = (Word *)leaf;
   const int32_t *ridx = d.ridx;
-  sf->last_bcast_copied = false;
+  sf_s::Compact *compact = nullptr;
   if (W == 1 && !sf->hp.corder.empty() && sf->nroots * (int64_t)sizeof(Word) >= kCompactRootBytes) {
     const int n = (int)sf->hp.corder.size();
-    if (Word *c = (Word *)compact_buffer(sf, (size_t)n * sizeof(Word), st)) {
+    if ((compact = compact_buffer(sf, (size_t)n * sizeof(Word), st))) {
+      Word *c = (Word *)compact->buf;
       hipLaunchKernelGGL((k_order_roots<Word>), dim3(nblocks((n + 3) / 4)), dim3(kBlock), 0, st, d.corder, n, r, c);
       r = c;
       ridx = d.cidx;
-      sf->last_bcast_copied = true;
     }
   }
 #define SF_MOVE(WW)                                                                                             \
@@ -702,6 +702,8 @@ static void bcast_move_w(sf_s *sf, int W, const void *root, void *leaf, hipStrea
     default: SF_MOVE(0); break;
   }
 #undef SF_MOVE
+  sf->last_bcast_copied = compact != nullptr;
+  if (compact) compact_done(compact, st);
 }
 
 template <typename T>

@@ -825,11 +825,12 @@ int analyze(sf_s *sf) {
 void free_device(sf_s *sf) {
   if (sf->dp.blob) (void)hipFree(sf->dp.blob);
   if (sf->scratch) (void)hipFree(sf->scratch);
-  if (sf->compact) (void)hipFree(sf->compact);
-  sf->compact = nullptr;
+  for (sf_s::Compact &c : sf->compact) {
+    if (c.buf) (void)hipFree(c.buf);
+    if (c.ev) (void)hipEventDestroy(c.ev);
+    c = sf_s::Compact{};
+  }
   sf->compact_bytes = 0;
-  sf->compact_bound = false;
-  sf->compact_stream = nullptr;
   for (void *p : sf->retired) (void)hipFree(p);
   sf->retired.clear();
   sf->dp = DevPlan{};
@@ -863,28 +864,51 @@ int ensure_scratch(sf_s *sf, size_t bytes) {
   return SF_OK;
 }
 
-void *compact_buffer(sf_s *sf, size_t bytes, hipStream_t st) {
-  if (st == hipStreamPerThread) return nullptr;  // one handle, a stream per thread
-  if (sf->compact_bound && sf->compact_stream != st) return nullptr;
+sf_s::Compact *compact_buffer(sf_s *sf, size_t bytes, hipStream_t st) {
+  if (bytes > sf->compact_bytes || st == hipStreamPerThread) return nullptr;  // (one handle, a stream per thread)
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
     (void)hipGetLastError();
     return nullptr;
   }
   if (cap != hipStreamCaptureStatusNone) return nullptr;
-  if (bytes > sf->compact_bytes) {
-    void *p = nullptr;
-    if (hipMalloc(&p, bytes) != hipSuccess) {
-      (void)hipGetLastError();
-      return nullptr;
-    }
-    if (sf->compact) sf->retired.push_back(sf->compact);  // enqueued work may still use it
-    sf->compact = p;
-    sf->compact_bytes = bytes;
+  for (sf_s::Compact &c : sf->compact)
+    if (c.uses > 0 && c.stream == st) return &c;
+  for (sf_s::Compact &c : sf->compact)
+    if (c.uses == 0) return &c;
+  // (relaxed: a query is refused while this process captures elsewhere)
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
   }
-  sf->compact_bound = true;
-  sf->compact_stream = st;
-  return sf->compact;
+  sf_s::Compact *got = nullptr;
+  for (sf_s::Compact &c : sf->compact) {
+    if (!got && c.marked && hipEventQuery(c.ev) == hipSuccess) got = &c;
+    c.wanted = true;
+  }
+  if (!got) (void)hipGetLastError();
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (got) {
+    got->uses = 0;
+    got->wanted = false;
+  }
+  return got;
+}
+
+// An event behind every Bcast would cost 3 us each (2M roots, 16M leaves: 57.0
+// -> 60.0 us; 1M roots, 2.5M leaves: 13.8 -> 16.9; 2.2 us as the launch's own
+// stop event), behind an SF's very first some 40 (154 -> 195).  So one is
+// recorded behind the owner's second to fourth Bcast (a warm-up on a side
+// stream leaves its buffer to others) and when another stream has asked since.
+void compact_done(sf_s::Compact *c, hipStream_t st) {
+  c->stream = st;
+  c->uses++;
+  c->marked = false;
+  if ((c->uses < 2 || c->uses > 4) && !c->wanted) return;
+  c->marked = hipEventRecord(c->ev, st) == hipSuccess;
+  if (!c->marked) (void)hipGetLastError();
+  c->wanted = false;
 }
 
 int acquire_scratch(sf_s *sf, size_t bytes, void **out) {
@@ -983,12 +1007,16 @@ int upload(sf_s *sf) {
     }
     off += (p.bytes + 255) / 256 * 256;
   }
-  if (!hp.corder.empty()) {  // not needed for a result: no error without it
-    const size_t bytes = hp.corder.size() * 8;
-    if (hipMalloc(&sf->compact, bytes) == hipSuccess) {
+  if (!hp.corder.empty()) {  // not needed for a result: no error without them
+    const size_t bytes = hp.corder.size() * 16;
+    bool all = true;
+    for (sf_s::Compact &c : sf->compact)
+      all = all && hipEventCreateWithFlags(&c.ev, hipEventDisableTiming) == hipSuccess &&
+            hipMalloc(&c.buf, bytes) == hipSuccess;
+    if (all) {
       sf->compact_bytes = bytes;
+      dp.bytes += 2 * bytes;
     } else {
-      sf->compact = nullptr;
       (void)hipGetLastError();
     }
   }

@@ -45,3 +45,50 @@ def test_capture(graph):
     with torch.cuda.graph(g):
         sf.bcast(root, leaf)
         assert sf.choices()["last_bcast_copied"] == 0
+
+
+def test_moves_between_streams(graph):
+    """Two streams have a copy each; a third gets one once the calls of its
+    last stream have completed."""
+    sf = S.StarForest(R, graph.iroot, None, graph.ranks).setup()
+    main, side, third = torch.cuda.current_stream(), torch.cuda.Stream(), torch.cuda.Stream()
+    roots = [torch.randn(R, dtype=torch.float64, device="cuda") for _ in range(2)]
+    index = torch.from_numpy(graph.iroot).cuda()
+    leaf = torch.zeros(L, dtype=torch.float64, device="cuda")
+
+    def call(stream, k):
+        leaf.zero_()
+        torch.cuda.synchronize()
+        sf.bcast(roots[k], leaf, stream=stream)
+        took = sf.choices()["last_bcast_copied"]
+        torch.cuda.synchronize()
+        assert torch.equal(leaf, roots[k][index])
+        return took
+
+    assert call(side, 0) == 1                          # a warm-up on a side stream
+    for k in range(3):
+        assert call(main, k & 1) == 1
+    assert call(third, 1) == 1                         # the main stream's, whose calls have completed
+    assert call(side, 0) == 1
+    for _ in range(20):
+        assert call(side, 1) == 1 and call(third, 0) == 1
+    assert call(main, 1) == 0                          # no event behind the owners' last calls yet
+    assert call(third, 0) == 1                         # this one hands its copy on
+    assert call(main, 1) == 1 and call(side, 0) == 1
+
+
+def test_set_up_allocates(graph):
+    """No Bcast allocates: the copy is part of the plan's device memory."""
+    sf = S.StarForest(R, graph.iroot, None, graph.ranks).setup()
+    touched = sf.choices()["degree_ordered"]
+    small = S.StarForest(3, [2, 0, 2]).setup()         # (the first launch loads the library's kernels)
+    small.bcast(torch.zeros(3, device="cuda"), torch.zeros(3, device="cuda"))
+    assert sf.info()["device_bytes"] >= 32 * touched + 4 * (touched + L)
+    for dtype, bs in ((torch.float64, 1), (torch.float64, 2), (torch.float32, 4)):
+        root = torch.zeros((R, bs), dtype=dtype, device="cuda")
+        leaf = torch.zeros((L, bs), dtype=dtype, device="cuda")
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        sf.bcast(root, leaf)
+        torch.cuda.synchronize()
+        assert sf.choices()["last_bcast_copied"] == 1 and torch.cuda.mem_get_info()[0] == free
