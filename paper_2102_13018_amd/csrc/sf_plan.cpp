@@ -458,34 +458,57 @@ int analyze(sf_s *sf) {
       while (t < n && at(t) > at(t - 1)) t++;
       if (t < n) to_sort.push_back((int32_t)s);
     }
-    if (!to_sort.empty()) {  // one walk over the slots hands the leaves to their segments in slot order
-      std::vector<int32_t> leaf_at(sf->leafspace, -1);
-      std::vector<uint16_t> lay_of;  // which of to_sort a leaf is in (one: all of its leaves)
-      std::vector<int64_t> fill(to_sort.size(), 0);
-      if (to_sort.size() == 1 && lay.size() == 1) {
-        for (int64_t i = 0; i < L; i++) leaf_at[slot(i)] = (int32_t)i;
-        lay[0].members.resize(L);
-      } else if (to_sort.size() < 65536) {
-        lay_of.resize(L);
-        for (size_t k = 0; k < to_sort.size(); k++)
-          for (int64_t i : lay[to_sort[k]].members) {
-            leaf_at[slot(i)] = (int32_t)i;
-            lay_of[i] = (uint16_t)k;
-          }
-      } else {
-        to_sort.clear();
+    // One walk over the slots hands the leaves to their segments in slot order;
+    // with few leaves on a wide leaf space (the walk takes 4 bytes and a step a
+    // slot) each segment's leaves are sorted instead.  The order decides speed
+    // only, so without memory for it a segment keeps the leaf order.
+    try {
+      struct Order {
+        std::vector<int64_t> members;
+        std::vector<int32_t> slots;
+      };
+      std::vector<Order> order(to_sort.size());
+      for (size_t k = 0; k < to_sort.size(); k++) {
+        const size_t n = lay[to_sort[k]].members.empty() ? (size_t)L : lay[to_sort[k]].members.size();
+        order[k].members.resize(n);
+        order[k].slots.resize(n);
       }
-      hp.slot_ordered = (int32_t)to_sort.size();
-      for (int32_t k : to_sort) lay[k].slots.resize(lay[k].members.size());
-      if (!to_sort.empty())
+      if (!to_sort.empty() && to_sort.size() < 65536 && sf->leafspace <= 4 * L + 65536) {
+        std::vector<int32_t> leaf_at(sf->leafspace, -1);
+        std::vector<uint16_t> lay_of;  // which of to_sort a leaf is in (one: all of its leaves)
+        std::vector<int64_t> fill(to_sort.size(), 0);
+        if (lay.size() == 1) {
+          for (int64_t i = 0; i < L; i++) leaf_at[slot(i)] = (int32_t)i;
+        } else {
+          lay_of.resize(L);
+          for (size_t k = 0; k < to_sort.size(); k++)
+            for (int64_t i : lay[to_sort[k]].members) {
+              leaf_at[slot(i)] = (int32_t)i;
+              lay_of[i] = (uint16_t)k;
+            }
+        }
         for (int64_t l = 0; l < sf->leafspace; l++) {
           const int32_t i = leaf_at[l];
           if (i < 0) continue;
           const int k = lay_of.empty() ? 0 : lay_of[i];
-          Lay &ly = lay[to_sort[k]];
-          ly.members[fill[k]] = i;
-          ly.slots[fill[k]++] = (int32_t)l;
+          order[k].members[fill[k]] = i;
+          order[k].slots[fill[k]++] = (int32_t)l;
         }
+      } else {
+        for (size_t k = 0; k < to_sort.size(); k++) {
+          const Lay &ly = lay[to_sort[k]];
+          std::vector<int64_t> &m = order[k].members;
+          for (size_t t = 0; t < m.size(); t++) m[t] = ly.members.empty() ? (int64_t)t : ly.members[t];
+          std::sort(m.begin(), m.end(), [&](int64_t a, int64_t b) { return slot(a) < slot(b); });
+          for (size_t t = 0; t < m.size(); t++) order[k].slots[t] = (int32_t)slot(m[t]);
+        }
+      }
+      for (size_t k = 0; k < to_sort.size(); k++) {
+        lay[to_sort[k]].members.swap(order[k].members);
+        lay[to_sort[k]].slots.swap(order[k].slots);
+      }
+      hp.slot_ordered = (int32_t)to_sort.size();
+    } catch (const std::bad_alloc &) {
     }
   }
 
