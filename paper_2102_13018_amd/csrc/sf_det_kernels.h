@@ -79,15 +79,22 @@ __device__ __forceinline__ T wave_chunk_tree(int lane, int n, Load load) {
 }
 
 // Every level above level 0 in one launch: a wavefront per root of at most
-// kChunk level-0 results, a block per root of more (at most kChunk * kChunk),
-// whose wavefronts take its level-1 chunks and leave their results in the LDS
-// for the last tree.  The chunk boundaries and trees are those of k_det_chunk
-// level by level.  Bound by the latency of its few dependent loads, which is
-// why one launch replaces one per level: 1.2M Zipf leaves of f32 2.1 + 3.0 ->
-// 3.5 us (the Reduce 22.3 -> 19.2), MAXLOC of 2M 35.4 -> 32.5, 16M f64 4.6 +
-// 4.8 -> 4.9 (123.3 -> 120.8).  Blocks of 16 wavefronts, so that the level-1
-// chunks of the hottest root (30 at 16M leaves) take two rounds.
+// kChunk level-0 results, a block per (root, unit component) of more (at most
+// kOneLaunchResults), whose wavefronts take its level-1 chunks and leave their
+// results in the LDS for the last tree.  The chunk boundaries and trees are
+// those of k_det_chunk level by level.  Bound by the latency of its few
+// dependent loads, which is why one launch replaces one per level: 1.2M Zipf
+// leaves of f32 2.1 + 3.0 -> 3.5 us (the Reduce 22.3 -> 19.2), MAXLOC of 2M
+// 35.4 -> 32.5, 16M f64 4.6 + 4.8 -> 4.9 (123.3 -> 120.8).  Blocks of 16
+// wavefronts, so that the level-1 chunks of such a root take at most two
+// rounds: with more a launch per level is as fast or faster (all leaves on one
+// root, f64: 2M leaves 22.6 us here, 22.7 with a launch per level; 4M leaves
+// 31.4 and 31.0; 16M leaves of two f32 147 and 97).  A block per component,
+// because the components of a wide unit would else wait for each other's
+// barriers (2M leaves of four f64 on one root 46.9 -> 32.1, a launch per level
+// 34.5; 300K of sixteen f32 43.5 -> 23.0, 38.4).
 constexpr int kLevelThreads = 1024;
+static_assert(kOneLaunchResults <= kChunk * kChunk, "one last tree per block");
 template <typename T, int OP>
 __global__ __launch_bounds__(kLevelThreads) void k_det_levels(const DevChunk *__restrict__ tops, int nbig, int ntops,
                                                               const T *__restrict__ seq, T *__restrict__ root, int bs) {
@@ -95,9 +102,9 @@ __global__ __launch_bounds__(kLevelThreads) void k_det_levels(const DevChunk *__
   __shared__ __align__(16) unsigned char raw[kChunk * sizeof(T)];
   T *part = reinterpret_cast<T *>(raw);
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const bool big = (int)blockIdx.x < nbig;
-  const int i = big ? (int)blockIdx.x : nbig + ((int)blockIdx.x - nbig) * kWaves + wv;
-  if (!big) {
+  const unsigned nb = (unsigned)nbig * (unsigned)bs;
+  if (blockIdx.x >= nb) {
+    const int64_t i = nbig + (int64_t)(blockIdx.x - nb) * kWaves + wv;
     if (i >= ntops) return;
     const DevChunk ch = tops[i];
     for (int c = 0; c < bs; c++) {
@@ -108,23 +115,21 @@ __global__ __launch_bounds__(kLevelThreads) void k_det_levels(const DevChunk *__
     }
     return;
   }
-  const DevChunk ch = tops[i];
+  const DevChunk ch = tops[blockIdx.x / (unsigned)bs];
+  const int c = (int)(blockIdx.x % (unsigned)bs);
   const int nc = (ch.n + kChunk - 1) / kChunk;
-  for (int c = 0; c < bs; c++) {
-    T *rp = root + (int64_t)ch.dst * bs + c;
-    const T r = ld(rp);
-    for (int j = wv; j < nc; j += kWaves) {
-      const int64_t e0 = (int64_t)ch.src + j * kChunk;
-      const T v = wave_chunk_tree<T, OP>(lane, min(kChunk, ch.n - j * kChunk),
-                                         [&](int e) { return ld(seq + (e0 + e) * bs + c); });
-      if (lane == 0) st(part + j, v);
-    }
-    __syncthreads();
-    if (wv == 0) {
-      const T v = wave_chunk_tree<T, OP>(lane, nc, [&](int e) { return ld(part + e); });
-      if (lane == 0) st(rp, Op<OP, T>::apply(r, v));
-    }
-    __syncthreads();
+  T *rp = root + (int64_t)ch.dst * bs + c;
+  const T r = ld(rp);
+  for (int j = wv; j < nc; j += kWaves) {
+    const int64_t e0 = (int64_t)ch.src + j * kChunk;
+    const T v = wave_chunk_tree<T, OP>(lane, min(kChunk, ch.n - j * kChunk),
+                                       [&](int e) { return ld(seq + (e0 + e) * bs + c); });
+    if (lane == 0) st(part + j, v);
+  }
+  __syncthreads();
+  if (wv == 0) {
+    const T v = wave_chunk_tree<T, OP>(lane, nc, [&](int e) { return ld(part + e); });
+    if (lane == 0) st(rp, Op<OP, T>::apply(r, v));
   }
 }
 template <typename T, int OP>
@@ -132,8 +137,8 @@ void launch_levels(const sf_s *sf, const T *seq, T *root, int bs, hipStream_t st
   const int n = (int)sf->hp.tops.size(), nbig = sf->hp.ntops_big;
   constexpr int kWaves = kLevelThreads / 64;
   if (n == 0) return;
-  hipLaunchKernelGGL((k_det_levels<T, OP>), dim3((unsigned)(nbig + (n - nbig + kWaves - 1) / kWaves)),
-                     dim3(kLevelThreads), 0, st, sf->dp.tops, nbig, n, seq, root, bs);
+  const unsigned g = (unsigned)nbig * (unsigned)bs + (unsigned)((n - nbig + kWaves - 1) / kWaves);
+  hipLaunchKernelGGL((k_det_levels<T, OP>), dim3(g), dim3(kLevelThreads), 0, st, sf->dp.tops, nbig, n, seq, root, bs);
 }
 
 // Large roots, pass 2: one wavefront per large root turns its chunk sums

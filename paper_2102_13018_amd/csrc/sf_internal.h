@@ -20,6 +20,7 @@ constexpr int kTileLeaves = 1024;    // largest work tile of the stream kernels 
 constexpr int kTileMin = 256;        // smallest work tile
 constexpr int kChunkLPT = 4;         // leaves per lane of the wave-chunk reduction
 constexpr int kChunk = 64 * kChunkLPT;  // leaves per aligned chunk (power of two)
+constexpr int kOneLaunchResults = 8192;  // most level-0 results of a root whose further levels share a launch
 constexpr int kSmallMaxDeg = 32;     // largest degree of the per-thread classes
 constexpr int kNumClasses = 6;       // degree classes 1, 2, 4, 8, 16, 32
 constexpr int kHotMax = 8192;        // candidate roots for LDS aggregation on the atomic path
@@ -149,8 +150,8 @@ struct HostPlan {
   int64_t scratch_len = 0;        // max sequence length written by a chunk level
   // roots with several level-0 results ({first, count, root} in level 0's
   // output): those of more than kChunk results first (ntops_big of them).
-  // Empty when some root has more than kChunk * kChunk results (its levels
-  // take a launch each).
+  // Empty when some root has more than kOneLaunchResults results (the levels
+  // then take a launch each).
   std::vector<DevChunk> tops;
   int32_t ntops_big = 0;
   // Reduce split for SFs whose repeated roots all have at most kSmallMaxDeg

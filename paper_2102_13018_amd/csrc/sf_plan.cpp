@@ -662,7 +662,7 @@ int analyze(sf_s *sf) {
             hp.ntops_big += big ? 1 : 0;
           }
       for (const Pend &p : next)
-        if (p.n > kChunk * kChunk) hp.tops.clear();
+        if (p.n > kOneLaunchResults) hp.tops.clear();
       if (hp.tops.empty()) hp.ntops_big = 0;
     }
     hp.levels.push_back(std::move(lv));
