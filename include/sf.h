@@ -448,6 +448,8 @@ typedef struct {
   int32_t rooted;            /* 1: Reduce walks the single-leaf roots in ascending order */
   int32_t slot_ordered;      /* segments whose leaves are walked in slot order */
   int32_t level_roots;       /* roots whose chunk levels above level 0 share a launch (0: a launch per level) */
+  int32_t line_runs[2];      /* partitioned units of at most 8 / 16 bytes: most windows' results that meet in one
+                                cache line of the roots where an order-free op takes no chunk levels */
 } sf_choices;
 int sf_get_choices(sf_t sf, sf_choices *choices);
 const char *sf_error_string(int code);

@@ -214,6 +214,7 @@ struct HostPlan {
     std::vector<int32_t> span_first;  // [nspan + 1]
     std::vector<int32_t> span_slot;
     std::vector<int32_t> span_root;   // [nspan]
+    int32_t line_runs = 0;            // most runs of the roots in one 128-byte line of the root array
     std::vector<int32_t> tile_leaf0;  // [ntiles] first slot if the tile's slots are contiguous, else -1
     std::vector<int32_t> pa_slot;     // [L] slot per processing position (only if some tile is not contiguous)
   } sp[2];

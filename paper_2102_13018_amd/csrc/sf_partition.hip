@@ -1249,8 +1249,16 @@ int launch_reduce_part(sf_s *sf, const T *leaf, T *root, int bs, bool atomic, hi
     // in deterministic mode where the order cannot show (a maximum or minimum
     // under the total order of the keys, which the integer atomics follow, and
     // wrapping sums): no chunk levels (1.2M Zipf leaves of f64: a sum with
-    // levels 26.7 us, a maximum without 22.2)
-    if (atomic || OrderFree<T, OP>::value) {
+    // levels 26.7 us, a maximum without 22.2).  The atomics of a root, or of
+    // the roots in one cache line, queue at 5 to 7 ns each, one per window and
+    // element, so there are levels where the fullest line takes more than the
+    // levels cost.  Maximum of 16M leaves of four i32, levels / without (us):
+    // Zipf 1.1 (1900 in the line) 222 / 229, on one root (15600) 177 / 288;
+    // two f64, Zipf 1.1 (950) 210 / 206; 4M leaves of two f32 on one root
+    // (1020) 35.5 / 35.3.  Single 8-byte elements gain up to twice that (16M
+    // f64 on one root, 1950: 86.3 / 83.9; f32 61.2 / 64.8).
+    const int64_t queue = (int64_t)hs.line_runs * bs, most = bs == 1 && sizeof(T) == 8 ? 2048 : 1024;
+    if (atomic || (OrderFree<T, OP>::value && queue <= most)) {
       rc = sp_reduce_launch<T, OP, true>(gw, pl, st, ds.win, ds.sroot, ds.wchunk, ds.lpos, (const T *)scr,
                                          buf[0], root, bs);
       if (rc) return rc;

@@ -296,6 +296,20 @@ static int build_stage(HostPlan &hp, HostPlan::Stage &sp, const std::vector<int3
     }
   }
   if (!sp.span_root.empty()) sp.span_first.push_back((int32_t)sp.span_slot.size());
+  // the most runs of spanning roots that share a 128-byte line of the root
+  // array (16 units of 8 bytes, 8 of 16)
+  {
+    const int32_t per = cap / 512;
+    std::vector<std::pair<int32_t, int32_t>> runs;  // (line, runs) per spanning root
+    for (size_t i = 0; i < sp.span_root.size(); i++)
+      runs.push_back({sp.span_root[i] / per, sp.span_first[i + 1] - sp.span_first[i]});
+    std::sort(runs.begin(), runs.end());
+    for (size_t i = 0, j = 0; i < runs.size(); i = j) {
+      int32_t sum = 0;
+      for (j = i; j < runs.size() && runs[j].first == runs[i].first; j++) sum += runs[j].second;
+      sp.line_runs = std::max(sp.line_runs, sum);
+    }
+  }
   if (sp.wcold < W) {
     for (int64_t s2 = sp.win[sp.wcold].base; s2 < L; s2++) sflag[s2] = 2;
   }

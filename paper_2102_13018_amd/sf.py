@@ -92,7 +92,8 @@ class SfInfo(ctypes.Structure):
 
 class SfChoices(ctypes.Structure):
     _fields_ = [("degree_ordered", ctypes.c_int64), ("last_bcast_copied", ctypes.c_int32),
-                ("rooted", ctypes.c_int32), ("slot_ordered", ctypes.c_int32), ("level_roots", ctypes.c_int32)]
+                ("rooted", ctypes.c_int32), ("slot_ordered", ctypes.c_int32), ("level_roots", ctypes.c_int32),
+                ("line_runs", ctypes.c_int32 * 2)]
 
 
 class SfBatchItem(ctypes.Structure):
@@ -442,7 +443,7 @@ class StarForest:
     def choices(self):
         c = SfChoices()
         check(lib().sf_get_choices(self.h, ctypes.byref(c)), "sf_get_choices")
-        return {f: getattr(c, f) for f, _ in c._fields_}
+        return {f: getattr(c, f) if f != "line_runs" else tuple(c.line_runs) for f, _ in c._fields_}
 
     def segment(self, s):
         seg = SfSegmentInfo()
