@@ -452,6 +452,9 @@ typedef struct {
                                 cache line of the roots where an order-free op takes no chunk levels */
 } sf_choices;
 int sf_get_choices(sf_t sf, sf_choices *choices);
+/* Column panels of a CSR matrix's product (0: the kernel with lanes per row)
+ * and its running sums per row (0 with 0 panels). */
+int sf_csr_get_choices(sf_csr_t a, int32_t *panels, int32_t *sums);
 const char *sf_error_string(int code);
 /* The HIP error behind the last SF_ERR_HIP of the calling thread. */
 int sf_last_hip_error(void);

@@ -30,6 +30,7 @@ struct sf_csr_s {
   // (panels 0: k_csr_spmv).  With several panels colidx / values hold that
   // order in place of the CSR order.
   int panels = 0;
+  int chains = 0;  // running sums per row: 4, 8 or 16
   int64_t ngroups = 0;
   uint32_t *gbase = nullptr;   // [ngroups * panels + 1] first entry of each group's panel
   uint16_t *starts = nullptr;  // [ngroups * panels * 64] first entry of each row, relative to gbase
@@ -60,9 +61,9 @@ __global__ __launch_bounds__(kBlock) void k_csr_spmv(const int64_t *__restrict__
 // y = A x (or y += A x) over one column panel, a wavefront per group of 64
 // rows: it loads the group's column indices and values coalesced, U * 64 at a
 // time, gathers x for all of them, and leaves (value, x) in its own part of
-// the LDS; each lane then sums its row's products there with four running
-// fused sums, combined pairwise.  No load depends on a row's own offset, so a
-// wavefront has U gathers per lane in flight whatever its rows' lengths.
+// the LDS; each lane then sums its row's products there.  No load depends on a
+// row's own offset, so a wavefront has U gathers per lane in flight whatever
+// its rows' lengths.
 //
 // Bound by the gathers: a request per entry, served from the L2 at 235 G/s
 // while x fits (190 beside the entry streams), at 115 G/s for an x of 8 MB and
@@ -73,15 +74,29 @@ __global__ __launch_bounds__(kBlock) void k_csr_spmv(const int64_t *__restrict__
 // with three, 124 with four.  2M rows (x of 16 MB): 411 with one panel, 254
 // with three, 248 with five.  250K rows x 16 entries: 51 -> 42; 1M rows x 4
 // entries over an x of 2 MB: 33.3 -> 30.3; 300K rows x 15 over 2.4 MB, the
-// matrix in the Infinity Cache: 30 -> 26.  Set aside: one launch whose
-// resident wavefronts sweep the panels together (no faster than 111 on warm
-// matrices against 92: they drift apart), panels bound to XCDs with partial
-// results (103 + 9 for their sum), the next group's loads issued ahead (108
-// against 108 on a matrix from HBM; fewer, longer wavefronts 120).  Sums of
-// fused products are closer to the exact ones than the lane tree of k_csr_spmv
-// (15 entries: 1.02e-16 against 1.10e-16; three panels 1.09e-16).
-constexpr int kCsrAcc = 4;
-template <int U>
+// matrix in the Infinity Cache: 30 -> 26; 1M rows of a 15-point stencil 69 ->
+// 34.  Set aside: one launch whose resident wavefronts sweep the panels
+// together (no faster than 111 on warm matrices against 92: they drift apart),
+// panels bound to XCDs with partial results (103 + 9 for their sum), the next
+// group's loads issued ahead (108 against 108 on a matrix from HBM; fewer,
+// longer wavefronts 120).
+//
+// C fused running sums per row, the last four of their additions and the one
+// to y with the roundings compensated: the error of a row is no larger than
+// that of the lane tree of k_csr_spmv at every length taken (root mean square
+// relative to the product, N(0,1) data, lane tree / here: 15 entries 1.11e-16 /
+// 0.88e-16, in three panels 0.85e-16, 32 entries 1.17e-16 / 1.11e-16, all C = 4;
+// 64 entries 1.28e-16 / 1.22e-16, C = 8; 128 entries 1.36e-16 / 1.33e-16, C =
+// 16).  1M rows of a 15-entry band take 34.9 us with C = 4, 36.3 with 8.
+// s += b, the rounding error added to c
+__device__ __forceinline__ void comp_add(double b, double &s, double &c) {
+#pragma clang fp contract(off)
+  const double t = s + b;
+  const double q = t - s;
+  c += (s - (t - q)) + (b - q);
+  s = t;
+}
+template <int U, int C>
 __global__ __launch_bounds__(kBlock) void k_csr_rows(const uint32_t *__restrict__ gbase,
                                                      const uint16_t *__restrict__ starts,
                                                      const int32_t *__restrict__ colidx,
@@ -103,7 +118,8 @@ __global__ __launch_bounds__(kBlock) void k_csr_rows(const uint32_t *__restrict_
   const int32_t *cb = colidx + b;
   const double *vb = values + b;
   int s1 = 0;
-  double acc[kCsrAcc] = {};
+  double s = y0, comp = 0.0;         // the row's sum and its compensation
+  double acc[C] = {};
   for (int c0 = 0; c0 < n; c0 += kCap) {
     // positions past n repeat the last entry; no row reads them
     int32_t col[U];
@@ -124,35 +140,50 @@ __global__ __launch_bounds__(kBlock) void k_csr_rows(const uint32_t *__restrict_
     // only the compiler has to keep them so
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     const int z = min(s1 - c0, kCap);
-    for (int j = max(s0 - c0, 0); j < z; j += kCsrAcc) {
-      double2 t[kCsrAcc];
+    for (int j = max(s0 - c0, 0); j < z; j += C) {
 #pragma unroll
-      for (int k = 0; k < kCsrAcc; k++) t[k] = lds[min(j + k, kCap - 1)];
+      for (int h = 0; h < C; h += 4) {
+        if (j + h >= z) break;
+        double2 t[4];
 #pragma unroll
-      for (int k = 0; k < kCsrAcc; k++) acc[k] = j + k < z ? fma(t[k].x, t[k].y, acc[k]) : acc[k];
+        for (int k = 0; k < 4; k++) t[k] = lds[min(j + h + k, kCap - 1)];
+#pragma unroll
+        for (int k = 0; k < 4; k++) acc[h + k] = j + h + k < z ? fma(t[k].x, t[k].y, acc[h + k]) : acc[h + k];
+      }
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   }
-  if (row < nrows) y[row] = y0 + ((acc[0] + acc[1]) + (acc[2] + acc[3]));
+#pragma unroll
+  for (int k = 0; k < 4; k++) {
+    double a = acc[k];
+    if constexpr (C == 8) a += acc[k + 4];
+    if constexpr (C == 16) a = (a + acc[k + 4]) + (acc[k + 8] + acc[k + 12]);
+    comp_add(a, s, comp);
+  }
+  // an infinite or NaN sum has no compensation
+  if (row < nrows) y[row] = comp - comp == 0.0 ? s + comp : s;
 }
 
 // The tables of k_csr_rows from the CSR arrays and, for several panels of pw
 // columns, the entries in (group, panel, row) order, a row's entries of a
 // panel in their stored order (pcol, pval).  A wavefront per group, a lane per
 // row; a group's entries stay in its range of the CSR arrays, so no scan over
-// the groups is needed.  Runs once per matrix.
+// the groups is needed.  longest: the most entries of a row in a panel (set to
+// 0 before).  Runs once per matrix.
 __global__ __launch_bounds__(kBlock) void k_csr_panelize(const int64_t *__restrict__ rowptr,
                                                          const int32_t *__restrict__ colidx,
                                                          const double *__restrict__ values, int64_t nrows,
                                                          int64_t ngroups, int panels, int pw,
                                                          uint32_t *__restrict__ gbase, uint16_t *__restrict__ starts,
-                                                         int32_t *__restrict__ pcol, double *__restrict__ pval) {
+                                                         int32_t *__restrict__ pcol, double *__restrict__ pval,
+                                                         int *__restrict__ longest) {
   const int lane = threadIdx.x & 63;
   const int64_t g = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
   if (g >= ngroups) return;
   const int64_t row = g * 64 + lane;
   const int64_t k0 = rowptr[min(row, nrows)], k1 = rowptr[min(row + 1, nrows)];
   int64_t base = rowptr[g * 64];
+  int most = 0;
   for (int p = 0; p < panels; p++) {
     const int32_t c0 = p * pw, c1 = p + 1 < panels ? c0 + pw : INT32_MAX;
     int cnt = 0;
@@ -160,6 +191,7 @@ __global__ __launch_bounds__(kBlock) void k_csr_panelize(const int64_t *__restri
       cnt = (int)(k1 - k0);
     else
       for (int64_t k = k0; k < k1; k++) cnt += colidx[k] >= c0 && colidx[k] < c1;
+    most = max(most, cnt);
     int inc = cnt;
 #pragma unroll
     for (int d = 1; d < 64; d *= 2) {
@@ -182,6 +214,9 @@ __global__ __launch_bounds__(kBlock) void k_csr_panelize(const int64_t *__restri
     base += __shfl(inc, 63);
   }
   if (g == ngroups - 1 && lane == 0) gbase[ngroups * panels] = (uint32_t)base;
+#pragma unroll
+  for (int d = 32; d > 0; d /= 2) most = max(most, __shfl_down(most, d));
+  if (lane == 0) atomicMax(longest, most);
 }
 
 static int pick_group(int64_t nrows, int64_t nnz) {
@@ -198,8 +233,11 @@ static int csr_launch(const sf_csr_s *a, const double *x, double *y, int accumul
   if (a->panels > 0) {
     // entries in flight: a whole group's panel where that is at most 384
     const bool four = a->nnz <= 256 * a->ngroups * a->panels;
+    const auto kernel = a->chains == 4   ? (four ? k_csr_rows<4, 4> : k_csr_rows<6, 4>)
+                        : a->chains == 8 ? (four ? k_csr_rows<4, 8> : k_csr_rows<6, 8>)
+                                         : (four ? k_csr_rows<4, 16> : k_csr_rows<6, 16>);
     for (int p = 0; p < a->panels; p++)
-      hipLaunchKernelGGL(four ? k_csr_rows<4> : k_csr_rows<6>, dim3(group_blocks(a->ngroups)), dim3(kBlock), 0, st,
+      hipLaunchKernelGGL(kernel, dim3(group_blocks(a->ngroups)), dim3(kBlock), 0, st,
                          a->gbase, a->starts, a->colidx, a->values, a->nrows, a->ngroups, a->panels, p, x, y,
                          accumulate || p > 0 ? 1 : 0);
     hipError_t e = hipGetLastError();
@@ -239,14 +277,15 @@ static void csr_free(sf_csr_s *a) {
 // Whether k_csr_rows takes the matrix, and with how many panels.
 //  * Rows of at most kCsrRowMean entries a panel on average, none far above
 //    that: a lane sums its row alone, so one long row would hold up its
-//    wavefront, and four running sums stay as exact as the lane tree only up
-//    to about that length.
+//    wavefront, and its running sums grow beyond the lane tree's error.
 //  * One panel while x is at most kCsrOnePanel bytes (500K rows x 15 entries
 //    over 4 MB: 46.9 us with one panel or two) or a group's columns lie within
 //    a panel's width (a band); else panels of about kCsrPanelBytes that leave
 //    a row kCsrPanelMin entries in each (every further panel reads and writes
 //    y once more).
 constexpr double kCsrRowMean = 24.0;
+constexpr int kCsrRowMost = 128;              // entries of a row in a panel
+constexpr int64_t kCsrRowMax = 1000;          // of a row in all panels (a group's starts are 16 bits)
 constexpr int64_t kCsrOnePanel = 9 << 19;     // 4.5 MiB; an XCD's L2 is 4 MiB
 constexpr int64_t kCsrPanelBytes = 11 << 18;  // 2.75 MiB
 constexpr double kCsrPanelMin = 4.0;
@@ -254,16 +293,18 @@ constexpr int kCsrPanelMax = 8;
 
 static int csr_panels(const sf_csr_s *a) {
   if (a->nnz == 0 || a->nnz >= INT32_MAX) return 0;
+  const int64_t groups = (a->nrows + 63) / 64;
   const double mean = (double)a->nnz / (double)a->nrows;
   int64_t longest = 0;
   for (int64_t i = 0; i < a->nrows; i++) longest = std::max(longest, a->h_rowptr[i + 1] - a->h_rowptr[i]);
+  if (longest > kCsrRowMax || (double)longest > 4.0 * mean + 32.0) return 0;
   int panels = 1;
   const int64_t xb = a->ncols * 8;
   if (xb > kCsrOnePanel) {
     const int64_t want = std::min<int64_t>((xb + kCsrPanelBytes - 1) / kCsrPanelBytes, kCsrPanelMax);
     panels = (int)std::max<int64_t>(1, std::min<int64_t>(want, (int64_t)(mean / kCsrPanelMin)));
     // mean column span of a sample of the groups
-    const int64_t groups = (a->nrows + 63) / 64, step = std::max<int64_t>(1, groups / 256);
+    const int64_t step = std::max<int64_t>(1, groups / 256);
     double span = 0.0;
     int64_t sampled = 0;
     for (int64_t g = 0; g < groups; g += step) {
@@ -275,8 +316,8 @@ static int csr_panels(const sf_csr_s *a) {
     }
     if (span * panels <= (double)a->ncols * (double)sampled) panels = 1;
   }
-  if (mean > kCsrRowMean * panels || (double)longest > 4.0 * mean + 32.0 || longest > 1000) return 0;
-  return panels;
+  if (panels == 1 && longest > kCsrRowMost) return 0;  // (several: csr_rows_plan looks at each panel)
+  return mean > kCsrRowMean * panels ? 0 : panels;
 }
 
 static int csr_rows_plan(sf_csr_s *a) {
@@ -284,30 +325,33 @@ static int csr_rows_plan(sf_csr_s *a) {
   if (panels == 0) return SF_OK;
   const int64_t ngroups = (a->nrows + 63) / 64;
   const size_t gp = (size_t)ngroups * panels;
-  uint32_t *gbase = nullptr;
+  uint32_t *gbase = nullptr;  // the word past its end: the most entries of a row in a panel
   uint16_t *starts = nullptr;
   int32_t *pcol = nullptr;
   double *pval = nullptr;
-  hipError_t e = hipMalloc(&gbase, (gp + 1) * sizeof(uint32_t));
+  int longest = 0;
+  hipError_t e = hipMalloc(&gbase, (gp + 2) * sizeof(uint32_t));
   if (e == hipSuccess) e = hipMalloc(&starts, gp * 64 * sizeof(uint16_t));
   if (e == hipSuccess && panels > 1) e = hipMalloc(&pcol, (size_t)a->nnz * 4);
   if (e == hipSuccess && panels > 1) e = hipMalloc(&pval, (size_t)a->nnz * 8);
+  if (e == hipSuccess) e = hipMemset(gbase + gp + 1, 0, sizeof(uint32_t));
   if (e == hipSuccess) {
     const int pw = (int)((a->ncols + panels - 1) / panels);
     hipLaunchKernelGGL(k_csr_panelize, dim3(group_blocks(ngroups)), dim3(kBlock), 0, nullptr, a->rowptr, a->colidx,
-                       a->values, a->nrows, ngroups, panels, pw, gbase, starts, pcol, pval);
+                       a->values, a->nrows, ngroups, panels, pw, gbase, starts, pcol, pval, (int *)(gbase + gp + 1));
     e = hipGetLastError();
-    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
-    if (e == hipSuccess && panels > 1) {
+    if (e == hipSuccess) e = hipMemcpy(&longest, gbase + gp + 1, sizeof(int), hipMemcpyDeviceToHost);
+    if (e == hipSuccess && panels > 1 && longest <= kCsrRowMost) {
       std::swap(a->colidx, pcol);
       std::swap(a->values, pval);
     }
   }
   if (pcol) (void)hipFree(pcol);
   if (pval) (void)hipFree(pval);
-  if (e != hipSuccess) {
+  if (e != hipSuccess || longest > kCsrRowMost) {
     if (gbase) (void)hipFree(gbase);
     if (starts) (void)hipFree(starts);
+    if (e == hipSuccess) return SF_OK;  // a row too long for a panel: k_csr_spmv serves the matrix
     if (e != hipErrorOutOfMemory) return set_hip_error(e);
     (void)hipGetLastError();  // no room for the tables: k_csr_spmv serves the matrix
     return SF_OK;
@@ -316,6 +360,7 @@ static int csr_rows_plan(sf_csr_s *a) {
   a->starts = starts;
   a->ngroups = ngroups;
   a->panels = panels;
+  a->chains = longest <= 32 ? 4 : longest <= 64 ? 8 : 16;
   return SF_OK;
 }
 
@@ -397,6 +442,13 @@ extern "C" int sf_csr_spmv(sf_csr_t a, const double *x, double *y, int32_t accum
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev != a->device) return SF_ERR_ARG;
   return csr_launch(a, x, y, accumulate ? 1 : 0, stream);
+}
+
+extern "C" int sf_csr_get_choices(sf_csr_t a, int32_t *panels, int32_t *sums) {
+  if (!a || !panels || !sums) return SF_ERR_ARG;
+  *panels = a->panels;
+  *sums = a->chains;
+  return SF_OK;
 }
 
 extern "C" int sf_csr_destroy(sf_csr_t *a) {

@@ -33,7 +33,7 @@ EXPORTS = [
     "sf_create", "sf_setup", "sf_set_reduce_mode", "sf_bcast_begin", "sf_bcast_end",
     "sf_reduce_begin", "sf_reduce_end", "sf_reduce_begin_noalloc", "sf_fetch_and_op_begin", "sf_fetch_and_op_end",
     "sf_get_multi_sf", "sf_gather_begin", "sf_gather_end", "sf_scatter_begin", "sf_scatter_end",
-    "sf_csr_create", "sf_csr_transpose", "sf_csr_spmv", "sf_csr_destroy", "sf_spmv", "sf_spmv_transpose",
+    "sf_csr_create", "sf_csr_transpose", "sf_csr_spmv", "sf_csr_get_choices", "sf_csr_destroy", "sf_spmv", "sf_spmv_transpose",
     "sf_get_graph", "sf_create_embedded_root_sf", "sf_create_embedded_leaf_sf", "sf_compose", "sf_compose_inverse",
     "sf_batch_create", "sf_batch_launch", "sf_batch_launch_separate", "sf_batch_graph_capture",
     "sf_batch_graph_launch", "sf_batch_autotune", "sf_batch_get_config", "sf_batch_set_config",
@@ -132,6 +132,7 @@ def lib():
         L.sf_csr_create.argtypes = [i64, i64, p, p, p, ctypes.POINTER(p)]
         L.sf_csr_transpose.argtypes = [p, ctypes.POINTER(p)]
         L.sf_csr_spmv.argtypes = [p, p, p, i32, p]
+        L.sf_csr_get_choices.argtypes = [p, ctypes.POINTER(i32), ctypes.POINTER(i32)]
         L.sf_csr_destroy.argtypes = [ctypes.POINTER(p)]
         L.sf_spmv.argtypes = [p, p, p, p, p, p, p, p]
         L.sf_spmv_transpose.argtypes = [p, p, p, p, p, p, p]
@@ -492,6 +493,12 @@ class Csr:
         check_buffer(y, self.nrows, SfUnit(SF_F64, 1), "y")
         check(lib().sf_csr_spmv(self.h, _ptr(x), _ptr(y), int(bool(accumulate)), _stream(stream)), "sf_csr_spmv")
         return y
+
+    def choices(self):
+        """(column panels, running sums per row) of sf_csr_get_choices."""
+        panels, sums = ctypes.c_int32(), ctypes.c_int32()
+        check(lib().sf_csr_get_choices(self.h, ctypes.byref(panels), ctypes.byref(sums)), "sf_csr_get_choices")
+        return panels.value, sums.value
 
     def destroy(self):
         if getattr(self, "h", None) and self.h.value:
