@@ -5,7 +5,8 @@
 //   y = M^T x:  y = A^T x, lvec = B^T x, then SFReduce SUM(lvec -> y).
 // The CSR products are plain HIP kernels: a wavefront per 64 short rows whose
 // entries it loads coalesced and sums out of the LDS (k_csr_rows, in column
-// panels when x does not fit an L2), or, for long or very uneven rows, G lanes
+// panels when x does not fit an L2), or, for small matrices and long or very
+// uneven rows, G lanes
 // of a wavefront per row (G a power of two near the mean row length), each
 // lane striding over the row's entries, the lanes' partial sums combined by
 // shuffles (k_csr_spmv).
@@ -274,15 +275,29 @@ static void csr_free(sf_csr_s *a) {
   delete a;
 }
 
-// Whether k_csr_rows takes the matrix, and with how many panels.
+// Whether k_csr_rows takes the matrix, and with how many panels (us,
+// k_csr_spmv / k_csr_rows):
+//  * Enough groups of rows to give every SIMD one and a half (100K rows x 9
+//    random entries 8.4 / 7.4, 70K rows 6.6 / 6.9, 10K rows x 24 5.4 / 7.2).
 //  * Rows of at most kCsrRowMean entries a panel on average, none far above
-//    that: a lane sums its row alone, so one long row would hold up its
-//    wavefront, and its running sums grow beyond the lane tree's error.
+//    that: a lane sums its row alone, so a long row holds up its wavefront,
+//    the more the fewer wavefronts there are beside it (2% of rows of 98
+//    entries among rows of 15: 150K rows 24.1 / 25, 300K 49.7 / 36.8, 1M 189 /
+//    111), and its running sums grow beyond the lane tree's error.  Rows of
+//    one entry are read coalesced by k_csr_spmv too (1M rows of a diagonal 5.8
+//    / 8.2).
 //  * One panel while x is at most kCsrOnePanel bytes (500K rows x 15 entries
 //    over 4 MB: 46.9 us with one panel or two) or a group's columns lie within
 //    a panel's width (a band); else panels of about kCsrPanelBytes that leave
 //    a row kCsrPanelMin entries in each (every further panel reads and writes
-//    y once more).
+//    y once more), given wavefronts for them (100K rows x 9 over 24 MB 17.7 /
+//    18.8, 300K rows over 8 MB 32.6 / 27.1).  With one panel over a wider x
+//    the gathers alone count, and k_csr_spmv has them all in flight where its
+//    lanes take an entry each (1M rows x 7 random entries 75.3 / 79.3, of 7 on
+//    average 86.3 / 80.7).
+constexpr int64_t kCsrMinGroups = 1536;
+constexpr int64_t kCsrEvenGroups = 4096;      // below: longest row 2 means + 16, from there 4 means + 32
+constexpr int64_t kCsrPanelGroups = 2048;     // several panels only from here
 constexpr double kCsrRowMean = 24.0;
 constexpr int kCsrRowMost = 128;              // entries of a row in a panel
 constexpr int64_t kCsrRowMax = 1000;          // of a row in all panels (a group's starts are 16 bits)
@@ -297,7 +312,8 @@ static int csr_panels(const sf_csr_s *a) {
   const double mean = (double)a->nnz / (double)a->nrows;
   int64_t longest = 0;
   for (int64_t i = 0; i < a->nrows; i++) longest = std::max(longest, a->h_rowptr[i + 1] - a->h_rowptr[i]);
-  if (longest > kCsrRowMax || (double)longest > 4.0 * mean + 32.0) return 0;
+  if (groups < kCsrMinGroups || longest <= 1 || longest > kCsrRowMax) return 0;
+  if ((double)longest > (groups < kCsrEvenGroups ? 2.0 * mean + 16.0 : 4.0 * mean + 32.0)) return 0;
   int panels = 1;
   const int64_t xb = a->ncols * 8;
   if (xb > kCsrOnePanel) {
@@ -314,7 +330,10 @@ static int csr_panels(const sf_csr_s *a) {
       span += (double)(*mm.second - *mm.first);
       sampled++;
     }
-    if (span * panels <= (double)a->ncols * (double)sampled) panels = 1;
+    const bool band = span * std::max(panels, 2) <= (double)a->ncols * (double)sampled;
+    if (band) panels = 1;
+    if (!band && panels == 1 && longest <= a->group) return 0;
+    if (panels > 1 && groups < kCsrPanelGroups) return 0;
   }
   if (panels == 1 && longest > kCsrRowMost) return 0;  // (several: csr_rows_plan looks at each panel)
   return mean > kCsrRowMean * panels ? 0 : panels;

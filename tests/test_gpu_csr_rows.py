@@ -1,5 +1,6 @@
-"""Products of matrices even enough for a wavefront per 64 rows: their rounding
-error is no larger than that of lanes per row; infinities and NaN."""
+"""Products of matrices large and even enough for a wavefront per 64 rows: which
+matrices take it, that its rounding error is no larger than that of lanes per
+row, and infinities and NaN."""
 import numpy as np
 import pytest
 
@@ -31,6 +32,37 @@ def matrix(rng, lens, ncols, band=0):
 
 def uneven(rng, nrows, short, long, part):
     return np.where(rng.random(nrows) < part, long, short)
+
+
+# (rows, columns, entries a row as (least, most) or (short, long, share of long), band) -> (panels, sums)
+@pytest.mark.parametrize("nrows,ncols,lens,band,want", [
+    (G * 1536, 5000, (3, 9), 0, (1, 4)), (G * 1535, 5000, (3, 9), 0, (0, 0)),        # wavefronts
+    (G * 1535 + 1, 5000, (9, 33), 0, (1, 8)), (G * 1600, 5000, (20, 65), 0, (0, 0)),  # the longest row
+    (G * 1536, 5000, (4, 40, 0.1), 0, (0, 0)), (G * 4096, 5000, (4, 40, 0.1), 0, (1, 8)),
+    (G * 4096, 5000, (11, 70, 0.1), 0, (1, 16)), (G * 4096, 5000, (11, 90, 0.02), 0, (0, 0)),
+    (G * 2048, 5000, (25, 25), 0, (0, 0)), (G * 2048, 5000, (24, 24), 0, (1, 4)),     # the mean row
+    (G * 4096, G * 4096, (1, 1), 0, (0, 0)),                                          # one entry a row
+    (G * 2047, 700_000, (12, 16), 0, (0, 0)), (G * 2048, 700_000, (12, 16), 0, (2, 4)),  # panels
+    (G * 2048, 1_300_000, (10, 30), 0, (4, 4)), (G * 2048, 3_000_000, (30, 34), 0, (8, 4)),
+    (G * 2048, 1_300_000, (10, 30), 60, (1, 4)),                                      # a band
+    (G * 2048, 700_000, (5, 5), 0, (0, 0)), (G * 2048, 700_000, (2, 9), 0, (1, 4))])  # one panel, a wide x
+def test_choices_and_results(nrows, ncols, lens, band, want):
+    rng = np.random.default_rng(nrows + ncols)
+    ln = uneven(rng, nrows, *lens) if len(lens) == 3 else rng.integers(lens[0], lens[1] + 1, nrows)
+    ln[0], ln[-1] = max(lens[:2]), max(lens[:2])
+    M = matrix(rng, ln, ncols, band)
+    A = S.Csr(nrows, ncols, *M)
+    assert A.choices() == want
+    x, y0 = rng.standard_normal(ncols), rng.standard_normal(nrows)
+    tx = torch.from_numpy(x).cuda()
+    scale = oracle.csr_spmv(M[0], M[1], np.abs(M[2]), np.abs(x)) + np.abs(y0)
+    for acc in (False, True):
+        ty = torch.from_numpy(y0).cuda()
+        A.spmv(tx, ty, accumulate=acc)
+        want_y = oracle.csr_spmv(*M, x, y0 if acc else None)
+        # any order of n <= 90 products and sums: (n + 8 panels) roundings of at most 2^-53 of the scale,
+        # on either side
+        assert np.all(np.abs(ty.cpu().numpy() - want_y) <= 2 * 100 * 2.0 ** -53 * scale)
 
 
 def test_row_too_long_for_a_panel():
