@@ -284,25 +284,25 @@ __device__ __forceinline__ int32_t seg_leaf_s(const DevSegment &s, const int32_t
 // so all U loads are in flight together: an index load inside a bounds check
 // is waited for before the next one is issued, and its wait drains the gather
 // issued before it.
-template <int U>
+template <int U, bool STREAM = true>
 __device__ __forceinline__ void seg_roots(const DevSegment &s, const int32_t *__restrict__ ridx, const int (&t)[U],
                                           int32_t (&r)[U]) {
   if (s.root.kind == SF_PATTERN_GENERIC) {
     const int32_t *p = ridx + s.roff;
 #pragma unroll
-    for (int u = 0; u < U; u++) r[u] = ld_stream(p + t[u]);
+    for (int u = 0; u < U; u++) r[u] = STREAM ? ld_stream(p + t[u]) : p[t[u]];
   } else {
 #pragma unroll
     for (int u = 0; u < U; u++) r[u] = pat_index(s.root, t[u]);
   }
 }
-template <int U>
+template <int U, bool STREAM = true>
 __device__ __forceinline__ void seg_leaves(const DevSegment &s, const int32_t *__restrict__ lidx, const int (&t)[U],
                                            int32_t (&l)[U]) {
   if (s.leaf.kind == SF_PATTERN_GENERIC) {
     const int32_t *p = lidx + s.loff;
 #pragma unroll
-    for (int u = 0; u < U; u++) l[u] = ld_stream(p + t[u]);
+    for (int u = 0; u < U; u++) l[u] = STREAM ? ld_stream(p + t[u]) : p[t[u]];
   } else {
 #pragma unroll
     for (int u = 0; u < U; u++) l[u] = pat_index(s.leaf, t[u]);

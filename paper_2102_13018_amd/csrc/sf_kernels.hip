@@ -92,7 +92,11 @@ __global__ __launch_bounds__(kBlock) void k_order_roots(const int32_t *__restric
     if (q0 + u * kBlock < n) out[q0 + u * kBlock] = v[u];
 }
 
-// leaf[l][c] = op(leaf[l][c], root[r][c]) element-wise.
+// leaf[l][c] = op(leaf[l][c], root[r][c]) element-wise.  The leaves are read and
+// written, so the indices compete with nothing that is used once only, and
+// reading them as streams costs the repeated call its cache hits (2.5M Zipf
+// leaves of f64 16.8 us as streams, 14.1 cached; 2.5M on sorted roots, two f64
+// 22.3, 17.1; 8M leaves of f32 on random roots 52.3, 47.2).
 template <typename T, int OP>
 __global__ __launch_bounds__(kBlock) void k_bcast_op(const DevSegment *__restrict__ segs,
                                                      const DevTile *__restrict__ tiles,
@@ -113,8 +117,8 @@ __global__ __launch_bounds__(kBlock) void k_bcast_op(const DevSegment *__restric
         c[u] = bs == 1 ? 0 : q % bs;
       }
       int32_t r[U], l[U];
-      seg_roots<U>(sg, ridx, t, r);
-      seg_leaves<U>(sg, lidx, t, l);
+      seg_roots<U, false>(sg, ridx, t, r);
+      seg_leaves<U, false>(sg, lidx, t, l);
       T rv[U], lv[U];
 #pragma unroll
       for (int u = 0; u < U; u++) {
@@ -242,8 +246,8 @@ __global__ __launch_bounds__(kBlock) void k_reduce_atomic(const DevSegment *__re
         t[u] = tl.t0 + q / bs;
         cc[u] = q % bs;
       }
-      seg_roots<U>(sg, ridx, t, rr);
-      seg_leaves<U>(sg, lidx, t, l);
+      seg_roots<U, false>(sg, ridx, t, rr);
+      seg_leaves<U, false>(sg, lidx, t, l);
 #pragma unroll
       for (int u = 0; u < U; u++) v[u] = leaf[(int64_t)l[u] * bs + cc[u]];
 #pragma unroll
@@ -472,8 +476,8 @@ __global__ __launch_bounds__(kBlock) void k_fop_atomic(const DevSegment *__restr
       c[u] = q % bs;
     }
     int32_t r[U], l[U];
-    seg_roots<U>(sg, ridx, t, r);
-    seg_leaves<U>(sg, lidx, t, l);
+    seg_roots<U, false>(sg, ridx, t, r);
+    seg_leaves<U, false>(sg, lidx, t, l);
     T v[U], got[U];
 #pragma unroll
     for (int u = 0; u < U; u++) v[u] = leaf[(int64_t)l[u] * bs + c[u]];
