@@ -447,6 +447,7 @@ typedef struct {
   int32_t last_bcast_copied; /* 1: the last Bcast REPLACE gathered from that copy */
   int32_t rooted;            /* 1: Reduce walks the single-leaf roots in ascending order */
   int32_t slot_ordered;      /* segments whose leaves are walked in slot order */
+  int32_t atomic_leaf_order; /* 1: the direct atomic kernels walk small units of repeated roots in leaf order */
   int32_t level_roots;       /* roots whose chunk levels above level 0 share a launch (0: a launch per level) */
   int32_t line_runs[2];      /* partitioned units of at most 8 / 16 bytes: most windows' results that meet in one
                                 cache line of the roots where an order-free op takes no chunk levels */

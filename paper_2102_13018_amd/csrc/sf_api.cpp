@@ -326,6 +326,7 @@ extern "C" int sf_get_choices(sf_t sf, sf_choices *choices) {
   choices->last_bcast_copied = sf->last_bcast_copied ? 1 : 0;
   choices->rooted = sf->hp.rooted ? 1 : 0;
   choices->slot_ordered = sf->hp.slot_ordered;
+  choices->atomic_leaf_order = sf->hp.aridx.empty() ? 0 : 1;
   choices->level_roots = (int32_t)sf->hp.tops.size();
   for (int c = 0; c < 2; c++) choices->line_runs[c] = sf->hp.sp[c].line_runs;
   return SF_OK;

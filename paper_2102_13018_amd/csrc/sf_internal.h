@@ -137,6 +137,7 @@ struct HostPlan {
   std::vector<int32_t> ridx;      // root index per processed leaf (generic root sides)
   std::vector<int32_t> ridx_hot;  // same, hot roots encoded as -(h+1)
   std::vector<int32_t> lidx;      // leaf slot per processed leaf (generic leaf sides)
+  std::vector<int32_t> aridx, aridx_hot, alidx;  // the three in leaf order, for the direct atomic kernels (or empty)
   std::vector<int32_t> hot_roots; // root id of hot slot h, by decreasing degree
   std::vector<int64_t> hot_deg;   // degree of hot slot h
   // root-sorted lists
@@ -228,6 +229,7 @@ struct DevPlan {
   DevTile *tiles = nullptr;
   int32_t *corder = nullptr, *cidx = nullptr;
   int32_t *ridx = nullptr, *ridx_hot = nullptr, *lidx = nullptr, *hot_roots = nullptr;
+  int32_t *aridx = nullptr, *aridx_hot = nullptr, *alidx = nullptr;
   int32_t *troot = nullptr, *toff = nullptr, *sl = nullptr;
   int32_t *cls[kNumClasses] = {};
   int32_t *large = nullptr;

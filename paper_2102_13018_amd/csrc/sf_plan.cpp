@@ -587,6 +587,39 @@ int analyze(sf_s *sf) {
     for (int64_t t0 = 0; t0 < n; t0 += tl)
       hp.tiles.push_back({(int32_t)s, (int32_t)t0, (int32_t)std::min<int64_t>(n, t0 + tl), 0});
   }
+  // The same arrays in leaf order, for the direct atomic kernels, whose atomics
+  // want the 64 leaves of a wavefront on few lines of the roots: where the leaf
+  // order has them there and the slot order has not.
+  if (hp.slot_ordered > 0 && sf->has_dup_roots && L < kPartitionMid) {
+    int64_t lines[2] = {0, 0};  // of the roots of 64 leaves at a time, leaf and slot order
+    std::vector<std::vector<int64_t>> by_leaf(lay.size());
+    for (size_t s = 0; s < lay.size(); s++) {
+      if (lay[s].slots.empty()) continue;
+      by_leaf[s] = lay[s].members;
+      std::sort(by_leaf[s].begin(), by_leaf[s].end());
+      const int64_t n = (int64_t)lay[s].members.size();
+      for (int64_t t0 = 0; t0 + 64 <= n; t0 += 64)
+        for (int o = 0; o < 2; o++) {
+          int32_t line[64];
+          for (int k = 0; k < 64; k++) line[k] = rt[(o == 0 ? by_leaf[s] : lay[s].members)[t0 + k]] / 16;
+          std::sort(line, line + 64);
+          lines[o] += std::unique(line, line + 64) - line;
+        }
+    }
+    if (lines[0] * 4 <= lines[1] * 3 && lines[1] > 0) {
+      hp.aridx = hp.ridx;
+      hp.aridx_hot = hp.ridx_hot;
+      hp.alidx = hp.lidx;
+      for (size_t s = 0; s < lay.size(); s++)
+        for (size_t t = 0; t < by_leaf[s].size(); t++) {
+          const int64_t i = by_leaf[s][t];
+          const int32_t r = rt[i];
+          hp.aridx[hp.dsegs[s].roff + t] = r;
+          if (!hp.aridx_hot.empty()) hp.aridx_hot[hp.dsegs[s].roff + t] = hot_of[r] >= 0 ? -(hot_of[r] + 1) : r;
+          hp.alidx[hp.dsegs[s].loff + t] = (int32_t)slot(i);
+        }
+    }
+  }
   // No repeated roots, and most leaves read their root from an index array:
   // Reduce walks the touched roots in ascending order (k_reduce_rooted).
   hp.rooted = !sf->has_dup_roots && 2 * (int64_t)hp.ridx.size() > L;
@@ -977,6 +1010,9 @@ int upload(sf_s *sf) {
   add(hp.corder.data(), hp.corder.size() * 4, (void **)&dp.corder);
   add(hp.cidx.data(), hp.cidx.size() * 4, (void **)&dp.cidx);
   add(hp.ridx_hot.data(), hp.ridx_hot.size() * 4, (void **)&dp.ridx_hot);
+  add(hp.aridx.data(), hp.aridx.size() * 4, (void **)&dp.aridx);
+  add(hp.aridx_hot.data(), hp.aridx_hot.size() * 4, (void **)&dp.aridx_hot);
+  add(hp.alidx.data(), hp.alidx.size() * 4, (void **)&dp.alidx);
   add(hp.lidx.data(), hp.lidx.size() * 4, (void **)&dp.lidx);
   add(hp.hot_roots.data(), hp.hot_roots.size() * 4, (void **)&dp.hot_roots);
   add(hp.troot.data(), hp.troot.size() * 4, (void **)&dp.troot);

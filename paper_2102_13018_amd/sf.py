@@ -92,7 +92,8 @@ class SfInfo(ctypes.Structure):
 
 class SfChoices(ctypes.Structure):
     _fields_ = [("degree_ordered", ctypes.c_int64), ("last_bcast_copied", ctypes.c_int32),
-                ("rooted", ctypes.c_int32), ("slot_ordered", ctypes.c_int32), ("level_roots", ctypes.c_int32),
+                ("rooted", ctypes.c_int32), ("slot_ordered", ctypes.c_int32),
+                ("atomic_leaf_order", ctypes.c_int32), ("level_roots", ctypes.c_int32),
                 ("line_runs", ctypes.c_int32 * 2)]
 
 
