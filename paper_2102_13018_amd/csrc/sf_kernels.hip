@@ -805,24 +805,27 @@ static int reduce_split_t(sf_s *sf, const T *leaf, T *root, int bs, hipStream_t 
   return check_launch();
 }
 
+template <typename T>
+static int reduce_replace_t(sf_s *sf, const T *leaf, T *root, int bs, hipStream_t st) {
+  const DevPlan &d = sf->dp;
+  const int64_t T_ = (int64_t)sf->hp.troot.size();
+  if (T_)
+    hipLaunchKernelGGL((k_det_replace<T>), dim3(nblocks(T_ * bs)), dim3(kBlock), 0, st, d.troot, (int)T_, d.toff, d.sl,
+                       leaf, root, bs);
+  return check_launch();
+}
+
 template <typename T, int OP>
 static int reduce_det_t(sf_s *sf, const T *leaf, T *root, int bs, hipStream_t st) {
   const DevPlan &d = sf->dp;
   const HostPlan &h = sf->hp;
   const size_t ub = sizeof(T) * (size_t)bs;
   if constexpr (!kIsHalf<T>) {  // 16-bit units are not partitioned
-    if (OP != OP_REPLACE && h.part_red_det && stage_class((int64_t)ub) >= 0 &&
+    if (h.part_red_det && stage_class((int64_t)ub) >= 0 &&
         scratch_fits(sf, part_scratch_need(sf, ub)))
       return launch_reduce_part<T, OP>(sf, leaf, root, bs, false, st);
   }
-  if (OP != OP_REPLACE && h.split && ub > kSplitMinUnit) return reduce_split_t<T, OP>(sf, leaf, root, bs, st);
-  if (OP == OP_REPLACE) {
-    const int64_t T_ = (int64_t)h.troot.size();
-    if (T_)
-      hipLaunchKernelGGL((k_det_replace<T>), dim3(nblocks(T_ * bs)), dim3(kBlock), 0, st, d.troot, (int)T_, d.toff,
-                         d.sl, leaf, root, bs);
-    return check_launch();
-  }
+  if (h.split && ub > kSplitMinUnit) return reduce_split_t<T, OP>(sf, leaf, root, bs, st);
   // scratch of the chunk levels first, so that nothing is enqueued when it
   // cannot be had
   T *buf[2] = {nullptr, nullptr};
@@ -944,7 +947,7 @@ static int reduce_t(sf_s *sf, int op, int mode, const void *leafv, void *rootv, 
   const bool dup = sf->has_dup_roots;
   if (op == SF_REPLACE) {
     if (!dup) return reduce_plain_t<T, OP_REPLACE>(sf, leaf, root, bs, st);
-    return reduce_det_t<T, OP_REPLACE>(sf, leaf, root, bs, st);
+    return reduce_replace_t<T>(sf, leaf, root, bs, st);
   }
 #define SF_RED(OPV)                                                        \
   do {                                                                     \
@@ -977,7 +980,9 @@ static int reduce_half_t(sf_s *sf, int op, const void *leafv, void *rootv, int b
     return reduce_det_t<T, OPV>(sf, leaf, root, bs, st);             \
   } while (0)
   switch (op) {
-    case SF_REPLACE: SF_RED(OP_REPLACE);
+    case SF_REPLACE:
+      if (!dup) return reduce_plain_t<T, OP_REPLACE>(sf, leaf, root, bs, st);
+      return reduce_replace_t<T>(sf, leaf, root, bs, st);
     case SF_SUM: SF_RED(OP_SUM);
     case SF_MAX: SF_RED(OP_MAX);
     case SF_MIN: SF_RED(OP_MIN);
@@ -1004,7 +1009,7 @@ int launch_reduce(sf_s *sf, sf_unit unit, const void *leaf, void *root, int op, 
       Pair *r = (Pair *)root;
       if (op == SF_REPLACE) {
         if (!sf->has_dup_roots) return reduce_plain_t<Pair, OP_REPLACE>(sf, l, r, unit.bs, st);
-        return reduce_det_t<Pair, OP_REPLACE>(sf, l, r, unit.bs, st);
+        return reduce_replace_t<Pair>(sf, l, r, unit.bs, st);
       }
       if (op == SF_MINLOC) {  // no atomic form: deterministic in every mode
         if (!sf->has_dup_roots) return reduce_plain_t<Pair, OP_MINLOC>(sf, l, r, unit.bs, st);
