@@ -22,6 +22,12 @@
 
 namespace sfi {
 
+// At most 80 scalar registers: with 81 to 96 a SIMD holds seven wavefronts of
+// these short kernels, not eight, and a launch of 7 to 8 blocks per CU runs in
+// two waves (Bcast SUM of 1.85M leaves of sixteen f32 69.7 us with 59
+// registers, 83.1 with 81, 68.9 limited; 480K leaves 17.3, 19.4, 17.8).
+#define SF_EIGHT_WAVES __attribute__((amdgpu_num_sgpr(80)))
+
 // ===================================================================== Bcast
 // leaf[l] = root[r] as W words of type Word per unit.  2^sh blocks per tile,
 // each taking its share of the tile's leaves, so that a block's threads have
@@ -98,7 +104,7 @@ __global__ __launch_bounds__(kBlock) void k_order_roots(const int32_t *__restric
 // leaves of f64 16.8 us as streams, 14.1 cached; 2.5M on sorted roots, two f64
 // 22.3, 17.1; 8M leaves of f32 on random roots 52.3, 47.2).
 template <typename T, int OP>
-__global__ __launch_bounds__(kBlock) void k_bcast_op(const DevSegment *__restrict__ segs,
+__global__ __launch_bounds__(kBlock) SF_EIGHT_WAVES void k_bcast_op(const DevSegment *__restrict__ segs,
                                                      const DevTile *__restrict__ tiles,
                                                      const int32_t *__restrict__ ridx,
                                                      const int32_t *__restrict__ lidx, const T *__restrict__ root,
@@ -137,7 +143,7 @@ __global__ __launch_bounds__(kBlock) void k_bcast_op(const DevSegment *__restric
 // root[r][c] = op(root[r][c], leaf[l][c]) without atomics: every root has at
 // most one leaf (no duplicate roots), or the op is REPLACE on such an SF.
 template <typename T, int OP>
-__global__ __launch_bounds__(kBlock) void k_reduce_plain(const DevSegment *__restrict__ segs,
+__global__ __launch_bounds__(kBlock) SF_EIGHT_WAVES void k_reduce_plain(const DevSegment *__restrict__ segs,
                                                          const DevTile *__restrict__ tiles,
                                                          const int32_t *__restrict__ ridx,
                                                          const int32_t *__restrict__ lidx,
@@ -219,7 +225,7 @@ __global__ __launch_bounds__(kBlock) void k_reduce_rooted(const int32_t *__restr
 // ridx_hot with h < nhot_lds are combined in this block's LDS first and
 // written with one device atomic per touched root when the block is done.
 template <typename T, int OP>
-__global__ __launch_bounds__(kBlock) void k_reduce_atomic(const DevSegment *__restrict__ segs,
+__global__ __launch_bounds__(kBlock) SF_EIGHT_WAVES void k_reduce_atomic(const DevSegment *__restrict__ segs,
                                                           const DevTile *__restrict__ tiles, int ntiles,
                                                           const int32_t *__restrict__ ridx,
                                                           const int32_t *__restrict__ lidx,
