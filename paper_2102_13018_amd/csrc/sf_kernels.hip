@@ -29,13 +29,14 @@ namespace sfi {
 #define SF_EIGHT_WAVES __attribute__((amdgpu_num_sgpr(80)))
 
 // ===================================================================== Bcast
-// leaf[l] = root[r] as W words of type Word per unit.  2^sh blocks per tile,
-// each taking its share of the tile's leaves, so that a block's threads have
-// about four words each and gather them all at once.  Bound by the lines that
-// the random root reads fetch into the L2s (128 bytes for an 8-byte root).
-// Measured with 1 / 2 / 4 blocks per 1024-leaf tile (us): 16M leaves of 8
-// bytes on Zipf roots 95.8 / 99.7 / 106.6; two Bcasts of 2M leaves of 64 bytes
-// in the k-NN layer 227.5 / 224.1 / 222.6 of the whole pass, 1.2M leaves of 64
+// leaf[l] = root[r] as W words of type Word per unit.  2^sh blocks per tile
+// (one, two or four), each taking its share of the tile's leaves: about four
+// words per thread, all gathered at once, for one to four words a unit; wider
+// units take rounds of four.  Bound by the lines that the random root reads
+// fetch into the L2s (128 bytes for an 8-byte root).  Measured with 1 / 2 / 4
+// blocks per 1024-leaf tile (us): 16M leaves of 8 bytes on Zipf roots, from the
+// roots themselves, 95.8 / 99.7 / 106.6; two Bcasts of 2M leaves of 64 bytes in
+// the k-NN layer 227.5 / 224.1 / 222.6 of the whole pass, 1.2M leaves of 64
 // bytes with their Reduce 66.2 / 64.7 / 63.6.
 template <typename Word, int W>
 __global__ __launch_bounds__(kBlock) void k_bcast_move(const DevSegment *__restrict__ segs,
@@ -385,7 +386,8 @@ __global__ __launch_bounds__(kBlock) void k_det_small_all(const int32_t *__restr
 // stay inside the condition here, unlike the other stream kernels': a tile
 // holds three items a thread or fewer of the short streams that take this
 // kernel, and the skipped and missing ones would cost loads of their own
-// (256^3 halo, bs 3, patterns: 11.2 us, 12.8 with unconditional loads).
+// (256^3 halo, bs 3, patterns: 11.2 to 11.8 us from run to run, 12.8 with
+// unconditional loads).
 template <typename T, int OP>
 __global__ __launch_bounds__(kBlock) void k_reduce_split(const DevSegment *__restrict__ segs,
                                                          const DevTile *__restrict__ tiles, int ntiles,
